@@ -10,9 +10,9 @@
 //                       length (its rows minus its rejected window entries)
 //                       and their running sum, the new cumulative offsets.
 //   varlen_compact      Family B: the flat [T][H][D] cache of every (layer,
-//                       K/V) is compacted into a second buffer, one sequence's
-//                       kept rows per span, in the split-piece layout of the
-//                       other out-of-place copies; extra workgroups write the
+//                       K/V) is compacted into a second buffer, in the
+//                       split-piece layout of the other out-of-place copies
+//                       laid over the whole output; extra workgroups write the
 //                       position ids (I2: each row's index in its sequence).
 #include "posmask.h"
 #include "span_copy.h"
@@ -106,6 +106,7 @@ struct VarlenArgs {
   u32x4* dst;
   int64_t src_slab_vecs, dst_slab_vecs;  // T_cap * H * D / 8 per (layer, K/V)
   int64_t row_vecs;                      // H * D / 8: one token row of the flat buffer
+  int32_t row_shift;                     // its logarithm when it is a power of two, else -1
   int64_t src_T, dst_T;
   const int32_t* cu_in;
   const int32_t* n_acc;
@@ -113,10 +114,10 @@ struct VarlenArgs {
   int64_t* pos;
   int32_t B, k, max_len;
   uint32_t* dev_status;
-  uint32_t chunks;        // workgroups per span
-  uint32_t span_base;
+  int64_t rows_cap;       // rows that the kept sequences can have in all
+  uint32_t chunks;        // workgroups per (layer, K/V) slab
+  uint32_t block_base;    // compaction workgroups of earlier launches
   uint32_t pos_blocks;    // position-id workgroups (first launch only)
-  uint32_t pos_col_blocks;
 };
 
 // Kept lengths and their running sum (one workgroup, B in stripes of 1024).
@@ -163,36 +164,98 @@ __global__ __launch_bounds__(kOneBlock) void varlen_offsets_kernel(VarlenArgs a)
   }
 }
 
+// The sequence whose kept rows hold output row r < cu_out[B]: the first one in
+// [lo, B) that ends beyond r.  `Load` reads cu_out (scalar loads for a
+// wave-uniform r).  A workgroup moves 2 KB, about 700 cycles of its SIMD's
+// time at full bandwidth, so the steps are few and 32-bit: comparing in vectors
+// (64-bit products) took 1062 us instead of 1045 over 6.95 GB, and a search that
+// probes seven offsets a round, for fewer dependent loads, 948 instead of 905
+// over 6.0 GB.
+template <typename Load>
+__device__ __forceinline__ int sequence_of(int32_t r, int lo, int B, Load cu_out) {
+  int hi = B - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (cu_out(mid + 1) > r) hi = mid;
+    else lo = mid + 1;
+  }
+  return lo;
+}
+
+// The output of a (layer, K/V) slab is one run of cu_out[B] rows, so it is
+// tiled as such, whatever the lengths: workgroups are laid over the rows that
+// the slab can hold (at most T, and at most B * max_len), in the split-piece
+// layout tiled from the slab's 16 KB boundary, and each finds its sequence by
+// a search in the offsets (scalar loads).  Tiling each sequence to the
+// longest one's length instead left 70% of the workgroups of a ragged batch
+// (32 sequences, lengths log-uniform in 64..4096) without work, and the
+// dispatch of empty workgroups bounded the kernel: 1510 us a call, against
+// 1045 with this tiling (6.95 GB; 8 sequences of U[128, 1024], 6.0 GB: 917 and
+// 905).  The search costs a few dependent loads: 64 sequences of 64-byte rows
+// (138 MB in all) take 26.6 us instead of 24.6.
 __global__ __launch_bounds__(kTpb) void varlen_compact_kernel(VarlenArgs a) {
-  uint32_t b = blockIdx.x;
+  const uint32_t b = blockIdx.x;
+  auto cu_scalar = [&](int i) { return load_invariant(a.cu_out + i); };
+  auto cu_lane = [&](int i) { return a.cu_out[i]; };
+  auto row_of = [&](int64_t u) {
+    return static_cast<int32_t>(a.row_shift >= 0 ? u >> a.row_shift : u / a.row_vecs);
+  };
+  // rows in all; offsets that do not come from disjoint sequences stop at the buffer
+  int64_t rows = cu_scalar(a.B);
+  if (rows > a.rows_cap) rows = a.rows_cap;
   if (b < a.pos_blocks) {
-    // position ids of one sequence's kept rows: 4*kTpb rows per workgroup
-    const uint32_t i = b / a.pos_col_blocks;
-    const uint32_t cb = b - i * a.pos_col_blocks;
-    const int64_t o = load_invariant(a.cu_out + i);
-    const int64_t keep = load_invariant(a.cu_out + i + 1) - o;
+    // position ids of the kept rows: 4*kTpb rows per workgroup
+    const int64_t r0 = static_cast<int64_t>(b) * (4 * kTpb);
+    if (r0 >= rows) return;
+    const int first = sequence_of(static_cast<int32_t>(r0), 0, a.B, cu_scalar);
+    const int64_t start = cu_scalar(first), end = cu_scalar(first + 1);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int64_t t = static_cast<int64_t>(cb) * (4 * kTpb) + q * kTpb + threadIdx.x;
-      if (t < keep) a.pos[o + t] = t;
+      const int64_t r = r0 + q * kTpb + threadIdx.x;
+      if (r < rows) a.pos[r] = r - (r < end ? start : cu_lane(sequence_of(static_cast<int32_t>(r), first, a.B, cu_lane)));
     }
     return;
   }
-  b -= a.pos_blocks;
-  const uint32_t rel = b / a.chunks;
-  const uint32_t sub = b - rel * a.chunks;
-  const uint32_t span = a.span_base + rel;                // (layer*2 + kv) * B + i
-  const uint32_t lk = span / static_cast<uint32_t>(a.B);
-  const int i = static_cast<int>(span - lk * static_cast<uint32_t>(a.B));
-  const int64_t o = load_invariant(a.cu_out + i);
-  const int64_t keep = load_invariant(a.cu_out + i + 1) - o;   // 0 for a skipped sequence
-  const int64_t from = load_invariant(a.cu_in + i);
-  const int64_t total = keep * a.row_vecs;
-  u32x4* d = a.dst + static_cast<int64_t>(lk) * a.dst_slab_vecs + o * a.row_vecs;
+  const uint32_t g = a.block_base + (b - a.pos_blocks);
+  const uint32_t lk = g / a.chunks;
+  const uint32_t sub = g - lk * a.chunks;
+  const int64_t total = rows * a.row_vecs;
+  u32x4* d = a.dst + static_cast<int64_t>(lk) * a.dst_slab_vecs;
+  const u32x4* s = a.src + static_cast<int64_t>(lk) * a.src_slab_vecs;
   const int64_t base = split_base<kPieces, kTpb, kSplit>(sub) - split_misalign<kPieces, kSplit>(d);
   if (base >= total) return;
-  split_pieces<kPieces, kTpb, kSplit, kNt>(a.src + static_cast<int64_t>(lk) * a.src_slab_vecs + from * a.row_vecs, d,
-                                           base, total, 0, 0);
+  const int t = threadIdx.x;
+  u32x4 v[kPieces] = {};
+  int seq = 0;
+  int64_t end = 0, move = 0;   // the sequence's end in the output, and how far its rows come from (vectors)
+#pragma unroll
+  for (int j = 0; j < kPieces; ++j) {
+    const int64_t p0 = base + static_cast<int64_t>(j) * kSplit;   // the piece's first vector (wave-uniform)
+    const int64_t first = p0 > 0 ? p0 : 0;
+    if (first >= total) break;
+    if (first >= end) {
+      seq = sequence_of(row_of(first), seq, a.B, cu_scalar);
+      end = static_cast<int64_t>(cu_scalar(seq + 1)) * a.row_vecs;
+      move = (static_cast<int64_t>(load_invariant(a.cu_in + seq)) - cu_scalar(seq)) * a.row_vecs;
+    }
+    const int64_t last = end < total ? end : total;
+    int64_t si = p0 + t;
+    if (si >= last && si < total) {   // a later sequence's rows begin inside the piece
+      const int q = sequence_of(row_of(si), seq, a.B, cu_lane);
+      si += (static_cast<int64_t>(a.cu_in[q]) - cu_lane(q)) * a.row_vecs;
+    } else {                          // lanes outside the slab read a vector that is there, and store nothing
+      si = (si < first ? first : (si >= last ? last - 1 : si)) + move;
+    }
+    v[j] = ld16<(kNt & 1) != 0>(s + si);
+  }
+#pragma unroll
+  for (int j = 0; j < kPieces; ++j) asm volatile("" ::"v"(v[j].x), "v"(v[j].y), "v"(v[j].z), "v"(v[j].w));
+#pragma unroll
+  for (int j = 0; j < kPieces; ++j) {
+    const int64_t p0 = base + static_cast<int64_t>(j) * kSplit;
+    const int64_t u = p0 + t;
+    if (u >= 0 && u < total) st16_at<(kNt & 2) != 0>(d + p0, t, v[j]);
+  }
 }
 
 }  // namespace
@@ -209,6 +272,7 @@ hipError_t launch_varlen_rollback(const VarlenLaunch& p, hipStream_t stream) {
   a.src = static_cast<const u32x4*>(p.src);
   a.dst = static_cast<u32x4*>(p.dst);
   a.row_vecs = static_cast<int64_t>(p.H) * p.D / 8;
+  a.row_shift = (a.row_vecs & (a.row_vecs - 1)) == 0 ? __builtin_ctzll(static_cast<uint64_t>(a.row_vecs)) : -1;
   a.src_slab_vecs = p.src_T * a.row_vecs;
   a.dst_slab_vecs = p.dst_T * a.row_vecs;
   a.src_T = p.src_T;
@@ -224,26 +288,24 @@ hipError_t launch_varlen_rollback(const VarlenLaunch& p, hipStream_t stream) {
   hipLaunchKernelGGL(varlen_offsets_kernel, dim3(1), dim3(kOneBlock), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  a.pos_col_blocks = static_cast<uint32_t>((static_cast<int64_t>(p.max_len) + 4 * kTpb - 1) / (4 * kTpb));
-  const int64_t pos_blocks = p.pos ? static_cast<int64_t>(a.pos_col_blocks) * p.B : 0;
-  const int64_t nspans = static_cast<int64_t>(p.L) * 2 * p.B;
-  // every span may start anywhere: room for the extra group of the aligned tiling
-  const int64_t chunks = split_blocks<kPieces, kTpb, kSplit>(static_cast<int64_t>(p.max_len) * a.row_vecs, true);
+  a.rows_cap = static_cast<int64_t>(p.max_len) * p.B < p.src_T ? static_cast<int64_t>(p.max_len) * p.B : p.src_T;
+  const int64_t pos_blocks = p.pos ? (a.rows_cap + 4 * kTpb - 1) / (4 * kTpb) : 0;
+  // a slab may start anywhere: room for the extra group of the aligned tiling
+  const int64_t chunks = split_blocks<kPieces, kTpb, kSplit>(a.rows_cap * a.row_vecs, true);
+  const int64_t blocks = static_cast<int64_t>(p.L) * 2 * chunks;
+  const int64_t most = max_launch_items() / kTpb;
+  if (most <= pos_blocks || blocks > 0xFFFFFFFFLL) return hipErrorInvalidConfiguration;
   a.chunks = static_cast<uint32_t>(chunks);
-  const int64_t per_launch = (max_launch_items() / kTpb - pos_blocks) / chunks;
-  if (per_launch < 1) return hipErrorInvalidConfiguration;
-  for (int64_t s0 = 0; s0 == 0 || s0 < nspans; s0 += per_launch) {
-    const int64_t ns = nspans - s0 < per_launch ? nspans - s0 : per_launch;
-    const bool first = s0 == 0;
-    a.span_base = static_cast<uint32_t>(s0);
-    a.pos_blocks = first ? static_cast<uint32_t>(pos_blocks) : 0u;
-    const int64_t blocks = ns * chunks + (first ? pos_blocks : 0);
-    if (blocks > 0) {
-      hipLaunchKernelGGL(varlen_compact_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(kTpb), 0, stream, a);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    if (ns <= 0) break;
+  a.pos_blocks = static_cast<uint32_t>(pos_blocks);
+  for (int64_t g = 0; g < blocks || a.pos_blocks > 0;) {
+    const int64_t room = most - a.pos_blocks;
+    const int64_t n = blocks - g < room ? blocks - g : room;
+    a.block_base = static_cast<uint32_t>(g);
+    hipLaunchKernelGGL(varlen_compact_kernel, dim3(static_cast<uint32_t>(n + a.pos_blocks)), dim3(kTpb), 0, stream, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    g += n;
+    a.pos_blocks = 0;
   }
   return hipSuccess;
 }

@@ -220,3 +220,28 @@ def test_varlen_rollback_full_size(sd):
         s1 = bits(src[l:l + 1])
         e, _, _ = oracle.varlen_rollback(s1, cu, n_acc, k)
         assert np.array_equal(bits(dst[l:l + 1])[:, :, : co[-1]], e[:, :, : co[-1]])
+
+
+# The output of a slab is tiled as one run: sequences of a few vectors, several
+# to a 64-vector piece and many to a 16 KB group, with skipped ones between
+# (their offsets repeat), a loose length bound, and launches of a few workgroups.
+@pytest.mark.parametrize("B,k,L,H,D,cmax,items", [(300, 0, 2, 1, 8, 3, 0), (300, 0, 2, 1, 8, 3, 64 * 40), (65, 2, 1, 3, 8, 90, 0),
+                                                  (130, 1, 2, 2, 64, 9, 64 * 13), (2, 3, 1, 2, 256, 70, 0)])
+def test_varlen_rollback_short_and_skipped_sequences(sd, monkeypatch, B, k, L, H, D, cmax, items):
+    rng = np.random.default_rng(B + D + items)
+    cu, src, n_acc, T, max_len = _varlen(rng, B, k, L, H, D, cmax=cmax)
+    bad = np.sort(rng.choice(np.arange(1, B), size=(B - 1) // 3, replace=False))
+    n_acc[bad] = k + 1
+    if items:
+        monkeypatch.setenv("SPECDEC_MAX_LAUNCH_ITEMS", str(items))
+    got, cu_out, pos = _run_varlen(sd, src, cu, n_acc, k, max_len * 3 + 1)
+    keep = np.diff(cu) - (k - n_acc)
+    keep[bad] = 0
+    ecu = np.concatenate([[0], np.cumsum(keep)])
+    assert np.array_equal(cu_out, ecu)
+    exp = np.full_like(src, SENT_KV)
+    epos = np.full(T, -1)
+    for i in range(B):
+        exp[:, :, ecu[i]: ecu[i + 1]] = src[:, :, cu[i]: cu[i] + keep[i]]
+        epos[ecu[i]: ecu[i + 1]] = np.arange(keep[i])
+    assert np.array_equal(got, exp) and np.array_equal(pos, epos)

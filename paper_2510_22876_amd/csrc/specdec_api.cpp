@@ -750,8 +750,9 @@ specdec_status_t step_greedy(const void* logits, int32_t dtype, const int32_t* d
   hipStream_t st = static_cast<hipStream_t>(stream);
   specdec::VerifyLaunch vp{logits, dtype, draft, pad_in, B, k, V, W_in, tokens, n_acc,
                            bonus, pad_out, w_new, workspace, dev_status};
-  // in place, the merge launch also writes the order the walk takes the rows in
-  vp.write_order = in_place && !fused_counts;
+  // where a walk realigns the cache in place, the merge launch also writes
+  // the order it takes the rows in
+  vp.write_order = in_place && !fused_counts && specdec::inplace_plan(src->L, B, src->H, src->D, W_in).chunks == 0;
   const int32_t* order =
       vp.write_order ? reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + specdec::order_offset(B, k, V))
                      : nullptr;

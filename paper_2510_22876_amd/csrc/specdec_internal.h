@@ -37,7 +37,16 @@ constexpr int kMaxOrderClasses = 8;
 // Byte offset of the order table in a verification workspace, and its size.
 int64_t order_offset(int64_t B, int64_t k, int64_t V);
 int64_t order_bytes(int64_t B);
-int64_t order_bytes(int64_t B);
+
+// How a cache is realigned in place: chunk by chunk (chunks > 0 workgroups a
+// span of `tpb` threads with `vec` 16-byte vectors each), or, with chunks =
+// 0, by one walk per span.
+struct InplacePlan {
+  int vec = 0, tpb = 0;
+  int lds = 0;          // bytes of LDS a workgroup claims to bound how many share a CU
+  int64_t chunks = 0;
+};
+InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in);
 
 struct RealignLaunch {
   const void* src;

@@ -12,9 +12,12 @@
 //   realign_oop        out-of-place unpad-append-repad of the bf16 KV cache:
 //                      one workgroup per 16 KB chunk of a (layer, K/V, row,
 //                      head) span, 128-bit loads and stores.
-//   realign_inplace    in-place variant: one workgroup walks a whole span in
-//                      the direction of its shift, a barrier between the reads
-//                      and the writes of each chunk.
+//   realign_inplace    in-place variant for many long spans: one workgroup
+//                      walks a whole span in the direction of its shift, a
+//                      barrier between the reads and the writes of each chunk.
+//   realign_chunk,     in-place variant for short spans and for few long ones:
+//   realign_strips     a workgroup per chunk of a span, all at once, then the
+//                      few vectors that cross from a chunk to the next.
 //   posmask blocks     position ids / mask of invariant I2, appended to either
 //                      realign grid (or launched alone).
 //
@@ -616,6 +619,7 @@ struct RealignArgs {
   uint32_t clear_count;
   const int32_t* order;                  // in place: verification's order table (NULL: the cache's order)
   uint32_t span_rows;                    // spans per row: L * 2 * H
+  uint32_t slots;                        // in place by chunks: spans * chunks
 };
 
 struct RowGeom {
@@ -782,13 +786,16 @@ __device__ __forceinline__ void hold(const u32x4& v) {
 
 // Loads chunk [lo, lo + kTpb*kVec) (clipped to [0, n); indices outside are
 // clamped, their values unused) of one row's kept vectors, which start at
-// `from` within the span.
+// `from` within the span.  A wave that is outside as a whole loads nothing
+// (ragged rows of 5..124 KB: 511 us a step with its loads, 425 without).
 template <int kVec, int kTpb, int kNt>
 __device__ __forceinline__ void load_chunk(const u32x4* base, int64_t from, int64_t lo, int64_t n, u32x4 (&v)[kVec]) {
-  const int64_t t0 = static_cast<int64_t>(threadIdx.x >> 6) * (64 * kVec) + (threadIdx.x & 63);
+  const int64_t w0 = lo + static_cast<int64_t>(wave_index()) * (64 * kVec);   // the wave's first vector
+  if (w0 >= n || w0 + 64 * kVec <= 0) return;   // the whole wave is outside
+  const int64_t t0 = w0 + (threadIdx.x & 63);
 #pragma unroll
   for (int j = 0; j < kVec; ++j) {
-    int64_t u = lo + t0 + j * 64;
+    int64_t u = t0 + j * 64;
     u = u < 0 ? 0 : (u >= n ? n - 1 : u);
     v[j] = ld16<(kNt & 1) != 0>(base + (from + u));
   }
@@ -905,6 +912,216 @@ __global__ __launch_bounds__(kTpb) void realign_inplace_kernel(RealignArgs a) {
     }
   }
   // columns [0, pad_out) already hold padding (+0.0) for a shift to lower addresses
+}
+
+// The first `count` vectors from `at` become padding.
+template <int kTpb, int kNt>
+__device__ __forceinline__ void zero_vectors(u32x4* at, int64_t count) {
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  const int lane = static_cast<int>(threadIdx.x & 63);
+  for (int64_t u0 = static_cast<int64_t>(wave_index()) * 64; u0 < count; u0 += kTpb)
+    if (u0 + lane < count) st16_at<(kNt & 2) != 0>(at + u0, static_cast<uint32_t>(lane), zero);
+}
+
+// Moves the vectors [0, n) at `at` by `shift` with one workgroup, chunk after
+// chunk in the direction of the shift.
+template <int kVec, int kTpb, int kNt>
+__device__ void walk_span(u32x4* at, int64_t n, int64_t shift) {
+  constexpr int64_t kChunk = static_cast<int64_t>(kTpb) * kVec;
+  u32x4 v[kVec];
+  for (int64_t it = 0; it < n; it += kChunk) {
+    const int64_t lo = shift > 0 ? n - it - kChunk : it;
+    load_chunk<kVec, kTpb, kNt>(at, 0, lo, n, v);
+#pragma unroll
+    for (int j = 0; j < kVec; ++j) hold(v[j]);
+    exec_barrier();   // every thread's loads have landed, and no later chunk's source meets this one's place
+    store_chunk<kVec, kTpb, kNt>(at, shift, lo, n, v);
+  }
+  if (shift > 0) zero_vectors<kTpb, kNt>(at, shift);
+}
+
+// A row's kept vectors [0, n) cut into chunks of whole 64-vector units, as even
+// as they come, each of at most `most` vectors.
+struct Chunks {
+  int64_t n, per, more;   // per units in a chunk, one more in the first `more`
+  int64_t count;
+  __device__ __forceinline__ Chunks(int64_t n_, int64_t most) : n(n_) {
+    const int64_t units = (n + 63) >> 6;
+    count = (n + most - 1) / most;
+    per = units / count;
+    more = units - per * count;
+  }
+  __device__ __forceinline__ int64_t lo(int64_t c) const {
+    const int64_t at = (c * per + (c < more ? c : more)) << 6;
+    return at < n ? at : n;
+  }
+  // the shortest chunk (the last one's last unit may be ragged)
+  __device__ __forceinline__ int64_t shortest() const { return n - lo(count - 1); }
+};
+
+// Workgroups start round-robin over the 8 XCDs, and which of the slots hold
+// work repeats along the grid (the rows that move, the chunks that a row has):
+// with 16 chunks a span, the first chunks of all spans would be one XCD's.
+// Slots are taken in groups of 8 neighbours, each group rotated over the XCDs
+// by the octal digit sum of its index, so that no power-of-two period meets
+// one XCD only.  (64 rows of 128..4096 columns, 16 chunks a span: 2140 us in
+// the grid's own order, 1225 so.)
+__device__ __forceinline__ uint32_t spread(uint32_t i, uint32_t slots) {
+  const uint32_t g = i >> 3;
+  const uint32_t r = g + (g >> 3) + (g >> 6) + (g >> 9) + (g >> 12) + (g >> 15) + (g >> 18);
+  return (i | 7u) < slots ? (g << 3) | ((i + r) & 7u) : i;
+}
+
+// In place, a chunk per workgroup, in two launches.  A span that fits one
+// chunk is loaded whole into registers and stored at its new place.  A longer
+// one is cut into chunks that move at the same time: each is loaded whole and
+// *rotated* by the shift d within its own bounds, so that no workgroup writes
+// what another reads.  All but d vectors of a chunk then lie where they
+// belong; the d that belong to the neighbour chunk lie in the place that the
+// shift vacated (its first d vectors for a shift to higher addresses, its
+// last d for one to lower), and realign_strips_kernel hands them over.  Where
+// a chunk is shorter than 2 d (a shift of many columns), one workgroup walks
+// the span instead.
+template <int kVec, int kTpb, int kNt, bool kMany>
+__global__ __launch_bounds__(kTpb) void realign_chunk_kernel(RealignArgs a) {
+  if (blockIdx.x < a.extra_blocks) {
+    extra_block<kTpb>(a, blockIdx.x);
+    return;
+  }
+  constexpr int kChunk = kTpb * kVec;
+  const uint32_t g = spread(a.span_base + (blockIdx.x - a.extra_blocks), a.slots);   // span * chunks + chunk
+  const uint32_t span = kMany ? g / a.chunks : g;
+  const int c = kMany ? static_cast<int>(g - span * a.chunks) : 0;
+  const uint32_t row = (span / static_cast<uint32_t>(a.H)) % static_cast<uint32_t>(a.B);
+  RowGeom geo;
+  const uint32_t err = row_geometry(a, static_cast<int>(row), geo);
+  if (err) {
+    if (c == 0 && span == row * static_cast<uint32_t>(a.H) && threadIdx.x == 0 && a.dev_status)
+      atomicOr(a.dev_status, err);
+    return;
+  }
+  const int64_t vpc = a.vpc;
+  const int64_t shift = static_cast<int64_t>(geo.pad_out - geo.pad_in) * vpc;
+  if (shift == 0) return;
+  const int64_t n = static_cast<int64_t>(geo.len) * vpc;
+  u32x4* at = a.dst + static_cast<int64_t>(span) * a.dst_span_vecs + static_cast<int64_t>(geo.pad_in) * vpc;
+  const int lane = static_cast<int>(threadIdx.x & 63);
+  const int wv = wave_index();
+  int64_t lo = 0;
+  int len = static_cast<int>(n < kChunk ? n : kChunk);
+  bool first = true, last = true;   // no chunk below / above: its vectors leave it for a place no chunk holds
+  if constexpr (kMany) {
+    if (n > kChunk) {
+      const Chunks ch(n, kChunk);
+      if (c >= ch.count) return;
+      const int64_t d = shift < 0 ? -shift : shift;
+      if (ch.shortest() < 2 * d) {
+        if (c == 0) walk_span<4, kTpb, kNt>(at, n, shift);
+        return;
+      }
+      lo = ch.lo(c);
+      len = static_cast<int>(ch.lo(c + 1) - lo);
+      first = c == 0;
+      last = c == ch.count - 1;
+    } else if (c > 0) {
+      return;
+    }
+  }
+  const int w0 = wv * (64 * kVec);   // the wave's first vector of the chunk
+  const u32x4* s = at + lo + w0;
+  // indices past the chunk are clamped, their values unused: a branch per load
+  // made the compiler write out a path for every count (227 registers, not 60)
+  u32x4 v[kVec] = {};
+  if (w0 < len) {
+    const int end = len - 1 - w0;
+#pragma unroll
+    for (int j = 0; j < kVec; ++j) v[j] = ld16<(kNt & 1) != 0>(s + (j * 64 + lane < end ? j * 64 + lane : end));
+  }
+#pragma unroll
+  for (int j = 0; j < kVec; ++j) hold(v[j]);
+  exec_barrier();   // every thread's loads have landed
+  const bool alone = first && last;
+  if (alone || n <= kChunk) {
+    u32x4* d = at + (lo + w0 + shift);
+#pragma unroll
+    for (int j = 0; j < kVec; ++j)
+      if (w0 + j * 64 + lane < len) st16_at<(kNt & 2) != 0>(d, static_cast<uint32_t>(j * 64 + lane), v[j]);
+    if (shift > 0) zero_vectors<kTpb, kNt>(at, shift);
+  } else {
+    const int d = static_cast<int>(shift);
+    u32x4* base = at + (lo - (first && d < 0 ? -d : 0));
+    const int off = first && d < 0 ? -d : 0;
+#pragma unroll
+    for (int j = 0; j < kVec; ++j) {
+      const int e = w0 + j * 64 + lane;
+      if (e < len) {
+        int to = e + d;
+        if (to >= len && !last) to -= len;
+        if (to < 0 && !first) to += len;
+        st16_at<(kNt & 2) != 0>(base, static_cast<uint32_t>(to + off), v[j]);
+      }
+    }
+  }
+}
+
+// Hands the strips that realign_chunk_kernel parked over to the neighbour
+// chunks, one workgroup per span.  For a shift to higher addresses, strip c
+// (the first d vectors of chunk c) goes to the first d vectors of chunk c+1,
+// and those of chunk 0 become padding; for one to lower addresses, strip c
+// (the last d of chunk c) goes to the last d of chunk c-1, and the end of the
+// row, which no column of the new row holds, is left as the walk leaves it:
+// with the vectors that moved away from there.  A batch of strips is loaded
+// before any is stored; a strip's place holds the strip that was loaded
+// before it.
+template <int kTpb, int kNt>
+__global__ __launch_bounds__(kTpb) void realign_strips_kernel(RealignArgs a, int most) {
+  constexpr int kVec = 4;
+  const uint32_t span = a.span_base + blockIdx.x;
+  const uint32_t row = (span / static_cast<uint32_t>(a.H)) % static_cast<uint32_t>(a.B);
+  RowGeom geo;
+  if (row_geometry(a, static_cast<int>(row), geo)) return;
+  const int64_t vpc = a.vpc;
+  const int64_t shift = static_cast<int64_t>(geo.pad_out - geo.pad_in) * vpc;
+  const int64_t n = static_cast<int64_t>(geo.len) * vpc;
+  if (shift == 0 || n <= most) return;
+  const Chunks ch(n, most);
+  const int64_t d64 = shift < 0 ? -shift : shift;
+  if (ch.shortest() < 2 * d64) return;   // walked
+  const uint32_t d = static_cast<uint32_t>(d64);
+  u32x4* at = a.dst + static_cast<int64_t>(span) * a.dst_span_vecs + static_cast<int64_t>(geo.pad_in) * vpc;
+  // strips to hand over: count - 1, and to lower addresses the row's end
+  const int64_t strips = ch.count - 1 + (shift < 0 ? 1 : 0);
+  const int64_t total = strips * d64;
+  for (int64_t t0 = 0; t0 < total; t0 += kTpb * kVec) {
+    u32x4 v[kVec];
+    int64_t to[kVec];
+#pragma unroll
+    for (int j = 0; j < kVec; ++j) {
+      const int64_t t = t0 + j * kTpb + threadIdx.x;
+      to[j] = -1;
+      if (t < total) {
+        const int64_t i = t / d;
+        const int64_t e = t - i * d64;
+        int64_t from;
+        if (shift > 0) {
+          const int64_t c = ch.count - 2 - i;
+          from = ch.lo(c) + e;
+          to[j] = ch.lo(c + 1) + e;
+        } else {
+          from = (i < ch.count - 1 ? ch.lo(i + 2) - d64 : n - 2 * d64) + e;
+          to[j] = ch.lo(i + 1) - d64 + e;
+        }
+        v[j] = ld16<(kNt & 1) != 0>(at + from);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kVec; ++j) hold(v[j]);
+    exec_barrier();
+#pragma unroll
+    for (int j = 0; j < kVec; ++j)
+      if (to[j] >= 0) st16_at<(kNt & 2) != 0>(at + to[j], 0u, v[j]);
+  }
+  if (shift > 0) zero_vectors<kTpb, kNt>(at, shift);
 }
 
 __global__ __launch_bounds__(kThreads) void posmask_kernel(int64_t* pos, uint8_t* mask,
@@ -1055,6 +1272,45 @@ static void fill_token_args(RealignArgs& a, const RealignLaunch& p, int tpb) {
   }
 }
 
+// The in-place plan, by the longest span a row can have and the number of
+// spans (the host does not know the rows' lengths).  Whole steps in us, one
+// box, walk / chunks of 64 KB / of 128 KB, the latter two with at most two
+// workgroups per CU (through LDS they do not use: more in flight spreads the
+// DRAM traffic and costs up to 15%), unless noted:
+//   spans of one chunk: to 22 KB 237 / 77 (no limit to two); to 60 KB, ragged
+//     580 / 138 (no limit), even ones 288 / 243; 5..124 KB, ragged 511 / 320 /
+//     272, even ones of 77..124 KB 416 / - / 433
+//   128 spans to 2 MB 74 / 52 / 61; 256 to 2 MB 113 / 104 / 111; 1536 of 0.45 MB
+//     101 / 93 / 97; 2048 to 0.9 MB 203 / 194 / 167; 4096 to 1 MB, ragged 365 /
+//     322 / 277, even 774 / 776 / 791; 8192 to 1 MB, ragged 620 / 582 / 498, even
+//     1336 / 1390 / 1383
+//   16384 to 0.9 MB, ragged 811 / 957 / 855; 14336 to 2 MB 2366 / 2785 / 2402
+// The walk's last round is long where few spans are long and the rest short;
+// the chunks pay the strips' bytes and launch.  The line lies where ragged
+// batches, the common ones, stop gaining; even ones lose 1 to 4% below it.
+InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in) {
+  InplacePlan plan;
+  const int64_t longest = W_in * (D / 8);   // a row holds at most W_in columns
+  const int64_t nspans = L * 2 * B * H;
+  if (longest <= 16 * 256) {
+    plan.vec = longest <= 4 * 256 ? 4 : (longest <= 8 * 256 ? 8 : 16);
+    plan.tpb = longest <= 4 * 64 ? 64 : 256;
+    plan.chunks = 1;
+    return plan;
+  }
+  if (longest > 32 * 256 && nspans > 8192) return plan;   // the walk
+  plan.vec = longest > 32 * 256 && nspans <= 1536 ? 16 : 32;
+  plan.tpb = 256;
+  plan.chunks = (longest + plan.vec * plan.tpb - 1) / (plan.vec * plan.tpb);
+  plan.lds = 64 * 1024;
+  return nspans * plan.chunks <= 0x7FFFFFFF ? plan : InplacePlan{};
+}
+
+template <int kVec, int kTpb, bool kMany>
+static void launch_chunks(const RealignArgs& a, dim3 grid, int lds, hipStream_t stream) {
+  hipLaunchKernelGGL((realign_chunk_kernel<kVec, kTpb, kInNt, kMany>), grid, dim3(kTpb), lds, stream, a);
+}
+
 hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
   RealignArgs a{};
   a.src = static_cast<const u32x4*>(p.src);
@@ -1078,7 +1334,10 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
   a.pm_cap = p.pm_cap;
   a.order = p.in_place ? p.order : nullptr;
   a.span_rows = static_cast<uint32_t>(static_cast<int64_t>(p.L) * 2 * p.H);
-  const int tpb = p.in_place ? kInTpb : kOopTpb;
+  const InplacePlan plan =
+      p.in_place ? inplace_plan(p.L, p.B, p.H, p.D, p.W_in) : InplacePlan{};
+  const bool by_chunk = plan.chunks > 0;
+  const int tpb = by_chunk ? plan.tpb : (p.in_place ? kInTpb : kOopTpb);
   int64_t pm_blocks = 0;
   a.pm_col_blocks = 1;
   if (p.pos) {
@@ -1091,12 +1350,54 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
   a.tok_blocks = static_cast<uint32_t>(tok_blocks);
   const int64_t extra = pm_blocks + tok_blocks + (a.clear_words ? 1 : 0);
   a.misaligned = !p.in_place && !split_spans_aligned<kOopVec, kOopSplit>(p.dst, a.dst_span_vecs);
-  const int64_t chunks = p.in_place ? 1 : split_blocks<kOopVec, kOopTpb, kOopSplit>(
+  const int64_t chunks = by_chunk ? plan.chunks : p.in_place ? 1 : split_blocks<kOopVec, kOopTpb, kOopSplit>(
                                                 static_cast<int64_t>(p.W_in) * a.vpc, a.misaligned != 0);
   a.chunks = static_cast<uint32_t>(chunks);
   // one dispatch holds fewer than 2^32 work-items: split the spans over
   // several launches when the cache is larger than that
   const int64_t max_blocks = (max_launch_items() / tpb) - extra;
+  if (by_chunk) {
+    // (the chunks of a span may fall into several launches)
+    if (max_blocks < 1) return hipErrorInvalidConfiguration;
+    const int64_t slots = nspans * chunks;
+    a.slots = static_cast<uint32_t>(slots);
+    a.extra_blocks = static_cast<uint32_t>(extra);
+    a.pm_blocks = static_cast<uint32_t>(pm_blocks);
+    for (int64_t g = 0; g < slots || a.extra_blocks > 0;) {
+      const int64_t n = slots - g < max_blocks ? slots - g : max_blocks;
+      a.span_base = static_cast<uint32_t>(g);
+      const dim3 grid(static_cast<uint32_t>(n + a.extra_blocks));
+      if (chunks > 1) {
+        if (plan.vec == 16) launch_chunks<16, 256, true>(a, grid, plan.lds, stream);
+        else launch_chunks<32, 256, true>(a, grid, plan.lds, stream);
+      } else if (plan.tpb == 64) {
+        launch_chunks<4, 64, false>(a, grid, plan.lds, stream);
+      } else {
+        switch (plan.vec) {
+          case 4: launch_chunks<4, 256, false>(a, grid, plan.lds, stream); break;
+          case 8: launch_chunks<8, 256, false>(a, grid, plan.lds, stream); break;
+          case 16: launch_chunks<16, 256, false>(a, grid, plan.lds, stream); break;
+          default: launch_chunks<32, 256, false>(a, grid, plan.lds, stream); break;
+        }
+      }
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      g += n;
+      a.extra_blocks = 0;
+    }
+    if (chunks > 1)
+      for (int64_t s0 = 0; s0 < nspans;) {
+        const int64_t most = max_launch_items() / kInTpb;
+        const int64_t n = nspans - s0 < most ? nspans - s0 : most;
+        a.span_base = static_cast<uint32_t>(s0);
+        hipLaunchKernelGGL((realign_strips_kernel<kInTpb, kInNt>), dim3(static_cast<uint32_t>(n)), dim3(kInTpb), 0,
+                           stream, a, plan.vec * plan.tpb);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        s0 += n;
+      }
+    return hipSuccess;
+  }
   const int64_t spans_per_launch = max_blocks / chunks;
   if (spans_per_launch < 1) return hipErrorInvalidConfiguration;
   const dim3 block(tpb);

@@ -289,3 +289,42 @@ def test_out_of_range_device_values_are_flagged():
     torch.cuda.synchronize()
     assert int(o.dev_status.cpu()[0]) & sd.DEV_BAD_ACCEPT
     assert bool((i16(dst2[:, :, 0]) == SENT_KV).all())
+
+
+def _inplace_case(W_in, ns, D=8, H=2, L=1, k=5):
+    return wl.Workload("inplace", B=len(ns), k=k, V=40, logit_dtype="f32", logit_std=1.0, L=L, H=H, D=D,
+                       prompt=("list", list(ns)), accept=("uniform",), W_in=W_in, extra_cap=7)
+
+
+# In place, spans of one chunk (16-byte vectors: 256, 1024, 2048, 4096, 8192),
+# of several (of 4096 vectors; of 8192 from 1536 spans on) with lengths at the
+# edges of a chunk, shifts of both signs (columns left of every row), shifts
+# too long for the chunks to hand over, and more spans than go by chunks.
+INPLACE_CASES = {
+    "one_256": _inplace_case(256, [250, 249, 63, 0, 200]), "one_257": _inplace_case(257, [251, 250, 64]),
+    "one_1024": _inplace_case(1024, [1018, 1017, 255]), "one_2048": _inplace_case(1025, [1019, 1000, 7]),
+    "one_4096": _inplace_case(4096, [4090, 4089, 2047]), "one_8192": _inplace_case(4097, [4091, 4090, 64]),
+    "one_8192_full": _inplace_case(8192, [8186, 8100, 12], D=8, H=1),
+    "many_edges": _inplace_case(12300, [12294, 8187, 8186, 8185, 4091, 4090, 4085, 12283, 5000]),
+    "many_d128": _inplace_case(1100, [1094, 1090, 767, 512, 511, 256, 30], D=128),
+    "many_left": _inplace_case(9000, [8400, 8100, 4090, 4096, 300], H=3),
+    "many_far_left": _inplace_case(12000, [8500, 8190, 4100, 10]),
+    "many_8192": _inplace_case(8400, [8394, 8190, 8186, 8000, 4000, 70, 8390, 8191], H=100),
+    "walk": _inplace_case(8200, [8194, 8193, 100, 8190], H=1025),
+}
+
+
+@pytest.mark.parametrize("name", sorted(INPLACE_CASES))
+def test_inplace_routes(name):
+    w = INPLACE_CASES[name]
+    for seed in (1, 4):
+        r = run_gpu(w, seed=seed, variant="inplace", tokens="inplace")
+        _full_check(r)
+        W = r.out["w_new"]
+        assert torch.equal(i16(r.dst[..., W:, :]), i16(r.src[..., W:, :])), "columns beyond the new width were written"
+
+
+def test_inplace_chunks_split_over_launches(monkeypatch):
+    for name, items in (("many_edges", 256 * 150), ("many_d128", 256 * 40)):
+        monkeypatch.setenv("SPECDEC_MAX_LAUNCH_ITEMS", str(items))
+        _full_check(run_gpu(INPLACE_CASES[name], seed=2, variant="inplace", tokens="inplace"))

@@ -24,11 +24,10 @@ namespace {
 constexpr uint32_t kBadPadIn = 0x1u, kBadAccept = 0x2u, kBadSlot = 0x10u, kSlotLen = 0x20u;
 
 // The gather and the whole-row write-back use the out-of-place realignment's
-// split-piece layout (64-thread workgroups, two 1 KB pieces 8 KB apart,
-// nontemporal loads and stores): the access pattern is the same.
+// split-piece layout (64-thread workgroups, two 1 KB pieces apart by
+// split_distance, nontemporal loads and stores): the access pattern is the same.
 constexpr int kTpb = 64;
 constexpr int kPieces = 2;
-constexpr int kSplit = 512;
 constexpr int kNt = 3;
 
 struct GatherArgs {
@@ -71,6 +70,7 @@ __device__ __forceinline__ int32_t gather_row_len(const GatherArgs& a, int row, 
   return n;
 }
 
+template <int kSplit>
 __global__ __launch_bounds__(kTpb) void gather_kernel(GatherArgs a) {
   uint32_t b = blockIdx.x;
   if (b < a.pm_blocks) {
@@ -208,6 +208,7 @@ __device__ __forceinline__ void span_of(const WritebackArgs& a, uint32_t span, i
 
 // Whole row: pool columns [0, n + a) of the slot receive batch columns
 // [pad, Lb + a) of the row, in the split-piece layout.
+template <int kSplit>
 __global__ __launch_bounds__(kTpb) void writeback_full_kernel(WritebackArgs a) {
   uint32_t b = blockIdx.x;
   if (b < a.meta_blocks) {
@@ -298,8 +299,10 @@ hipError_t launch_gather(const GatherLaunch& p, hipStream_t stream) {
   const int64_t tok_blocks = static_cast<int64_t>(a.tok_col_blocks) * p.B;
   const int64_t extra = pm_blocks + tok_blocks;
   const int64_t nspans = p.Lb > 0 ? static_cast<int64_t>(p.L) * 2 * p.B * p.H : 0;
-  a.misaligned = !split_spans_aligned<kPieces, kSplit>(p.batch, a.batch_span_vecs);
-  const int64_t chunks = split_blocks<kPieces, kTpb, kSplit>(static_cast<int64_t>(p.Lb) * a.vpc, a.misaligned != 0);
+  const int64_t row_vecs = static_cast<int64_t>(p.Lb) * a.vpc;
+  const int split = split_distance(nspans, row_vecs, true);
+  a.misaligned = !split_spans_aligned(kPieces, split, p.batch, a.batch_span_vecs);
+  const int64_t chunks = split_blocks(kPieces, kTpb, split, row_vecs, a.misaligned != 0);
   a.chunks = static_cast<uint32_t>(chunks > 0 ? chunks : 1);
   const int64_t max_blocks = max_launch_items() / kTpb - extra;
   const int64_t per_launch = max_blocks / a.chunks;
@@ -312,7 +315,10 @@ hipError_t launch_gather(const GatherLaunch& p, hipStream_t stream) {
     a.tok_blocks = first ? static_cast<uint32_t>(tok_blocks) : 0u;
     const int64_t blocks = ns * a.chunks + (first ? extra : 0);
     if (blocks > 0) {
-      hipLaunchKernelGGL(gather_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(kTpb), 0, stream, a);
+      const dim3 grid(static_cast<uint32_t>(blocks));
+      if (split == 64) hipLaunchKernelGGL(gather_kernel<64>, grid, dim3(kTpb), 0, stream, a);
+      else if (split == 512) hipLaunchKernelGGL(gather_kernel<512>, grid, dim3(kTpb), 0, stream, a);
+      else hipLaunchKernelGGL(gather_kernel<1024>, grid, dim3(kTpb), 0, stream, a);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
@@ -347,9 +353,10 @@ hipError_t launch_writeback(const WritebackLaunch& p, hipStream_t stream) {
   const int64_t nspans = static_cast<int64_t>(p.L) * 2 * p.B * p.H;
   const int64_t extra = p.B;
   int64_t chunks = 1;
-  a.misaligned = !p.append_only && !split_spans_aligned<kPieces, kSplit>(p.pool, a.pool_span_vecs);
-  if (!p.append_only)
-    chunks = split_blocks<kPieces, kTpb, kSplit>((static_cast<int64_t>(p.Lb) + p.k + 1) * a.vpc, a.misaligned != 0);
+  const int64_t row_vecs = (static_cast<int64_t>(p.Lb) + p.k + 1) * a.vpc;
+  const int split = split_distance(nspans, row_vecs, false);
+  a.misaligned = !p.append_only && !split_spans_aligned(kPieces, split, p.pool, a.pool_span_vecs);
+  if (!p.append_only) chunks = split_blocks(kPieces, kTpb, split, row_vecs, a.misaligned != 0);
   a.chunks = static_cast<uint32_t>(chunks);
   const int64_t max_blocks = max_launch_items() / kTpb - extra;
   const int64_t per_launch = max_blocks / chunks;
@@ -361,10 +368,10 @@ hipError_t launch_writeback(const WritebackLaunch& p, hipStream_t stream) {
     a.meta_blocks = first ? static_cast<uint32_t>(extra) : 0u;
     const int64_t blocks = ns * chunks + (first ? extra : 0);
     if (blocks > 0) {
-      if (p.append_only)
-        hipLaunchKernelGGL(writeback_append_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(kTpb), 0, stream, a);
-      else
-        hipLaunchKernelGGL(writeback_full_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(kTpb), 0, stream, a);
+      const dim3 grid(static_cast<uint32_t>(blocks));
+      if (p.append_only) hipLaunchKernelGGL(writeback_append_kernel, grid, dim3(kTpb), 0, stream, a);
+      else if (split == 64) hipLaunchKernelGGL(writeback_full_kernel<64>, grid, dim3(kTpb), 0, stream, a);
+      else hipLaunchKernelGGL(writeback_full_kernel<512>, grid, dim3(kTpb), 0, stream, a);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

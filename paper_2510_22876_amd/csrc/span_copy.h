@@ -112,10 +112,32 @@ __device__ __forceinline__ int64_t split_base(uint32_t sub) {
 // Workgroups per span in the split-piece layout for spans of `vecs` vectors;
 // with `misaligned`, room for one more group (a span tiled from the group
 // boundary below its start).
+inline int64_t split_blocks(int pieces, int tpb, int split, int64_t vecs, bool misaligned = false) {
+  const int64_t group = static_cast<int64_t>(pieces) * split;
+  return ((vecs + (misaligned ? group - 1 : 0) + group - 1) / group) * (split / tpb);
+}
 template <int kPieces, int kTpb, int kSplit>
-constexpr int64_t split_blocks(int64_t vecs, bool misaligned = false) {
-  constexpr int64_t kGroup = static_cast<int64_t>(kPieces) * kSplit;
-  return ((vecs + (misaligned ? kGroup - 1 : 0) + kGroup - 1) / kGroup) * (kSplit / kTpb);
+inline int64_t split_blocks(int64_t vecs, bool misaligned = false) {
+  return split_blocks(kPieces, kTpb, kSplit, vecs, misaligned);
+}
+
+// Distance in vectors between the two pieces of a workgroup, for `spans`
+// output spans of at most `vecs` vectors each; `padded`: every span is
+// written to that length.  Measured, whole calls in us at 64 / 512 / 1024:
+//   8192 spans of 17 KB 51.1 / 58.5 / 80.8 (147 MB), 2048 of 34 KB 30.5 / 33.6 /
+//     33.1 (70 MB), 4096 of 63 KB 78.7 / 76.5 / - (262 MB): small caches, where
+//     the workgroups that a coarse group rounds up to cost more than the
+//     memory's access pattern;
+//   16384 spans of 60 KB 340 / 306 / 299, 67584 of 59 KB 798 / 745 / 877, 16384
+//     of 120 KB 623 / 590 / 587: 512;
+//   16384 spans of 0.9 MB 3492 / 2819 / 2786, 2048 of 0.9 MB 381 / 367 / 362: long
+//     padded spans, where a group of 32 KB rounds up little (16384 of 260 KB
+//     1185 / 1129 / 1131).  Where rows end as they come (a write-back of 16 rows
+//     of 64..4096 columns) it leaves more workgroups empty: 989 / 1016 at 512 /
+//     1024.
+inline int split_distance(int64_t spans, int64_t vecs, bool padded) {
+  if (spans * vecs * 16 <= (192ll << 20)) return 64;
+  return padded && vecs >= 16 * 1024 ? 1024 : 512;
 }
 
 // Output spans are tiled in groups of kPieces*kSplit vectors.  When a span
@@ -135,11 +157,9 @@ __device__ __forceinline__ int64_t split_misalign(const u32x4* d) {
 
 // True when every span of a buffer (base pointer, span stride in vectors)
 // starts on a group boundary, so no span needs the extra group.
-template <int kPieces, int kSplit>
-inline bool split_spans_aligned(const void* base, int64_t span_vecs) {
-  constexpr uint64_t kGroup = static_cast<uint64_t>(kPieces) * kSplit;
-  return (reinterpret_cast<uintptr_t>(base) % (kGroup * 16u)) == 0 &&
-         (static_cast<uint64_t>(span_vecs) % kGroup) == 0;
+inline bool split_spans_aligned(int pieces, int split, const void* base, int64_t span_vecs) {
+  const uint64_t group = static_cast<uint64_t>(pieces) * split;
+  return (reinterpret_cast<uintptr_t>(base) % (group * 16u)) == 0 && (static_cast<uint64_t>(span_vecs) % group) == 0;
 }
 
 }  // namespace specdec

@@ -554,8 +554,6 @@ __global__ __launch_bounds__(kFusedThreads) void verify_fused_kernel(FusedVerify
 //   *_VEC  16-byte vectors per lane per chunk (out of place: pieces per
 //          workgroup)
 //   *_TPB  threads per workgroup (a multiple of 64)
-//   OOP_SPLIT  distance in vectors between the pieces of an out-of-place
-//          workgroup
 //   *_NT   nontemporal hints (the cache is streamed once): bit 0 on loads,
 //          bit 1 on stores
 // Small, in-order workgroups keep the set of DRAM rows touched at any moment
@@ -568,9 +566,6 @@ __global__ __launch_bounds__(kFusedThreads) void verify_fused_kernel(FusedVerify
 #endif
 #ifndef SPECDEC_OOP_TPB
 #define SPECDEC_OOP_TPB 64
-#endif
-#ifndef SPECDEC_OOP_SPLIT
-#define SPECDEC_OOP_SPLIT 512
 #endif
 #ifndef SPECDEC_OOP_NT
 #define SPECDEC_OOP_NT 3
@@ -1142,7 +1137,6 @@ __global__ __launch_bounds__(kThreads) void zero_kernel(uint4* p16, int64_t n16,
 }
 
 constexpr int kOopVec = SPECDEC_OOP_VEC, kOopTpb = SPECDEC_OOP_TPB, kOopNt = SPECDEC_OOP_NT;
-constexpr int kOopSplit = SPECDEC_OOP_SPLIT;
 constexpr int kInVec = SPECDEC_INPLACE_VEC, kInTpb = SPECDEC_INPLACE_TPB, kInNt = SPECDEC_INPLACE_NT;
 static_assert(kOopTpb % 64 == 0 && kInTpb % 64 == 0, "workgroups are whole wavefronts");
 
@@ -1349,9 +1343,11 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
   const int64_t tok_blocks = static_cast<int64_t>(a.tok_col_blocks) * p.B;
   a.tok_blocks = static_cast<uint32_t>(tok_blocks);
   const int64_t extra = pm_blocks + tok_blocks + (a.clear_words ? 1 : 0);
-  a.misaligned = !p.in_place && !split_spans_aligned<kOopVec, kOopSplit>(p.dst, a.dst_span_vecs);
-  const int64_t chunks = by_chunk ? plan.chunks : p.in_place ? 1 : split_blocks<kOopVec, kOopTpb, kOopSplit>(
-                                                static_cast<int64_t>(p.W_in) * a.vpc, a.misaligned != 0);
+  const int64_t row_vecs = static_cast<int64_t>(p.W_in) * a.vpc;   // a span's output is at most this long
+  const int split = split_distance(nspans, row_vecs, true);
+  a.misaligned = !p.in_place && !split_spans_aligned(kOopVec, split, p.dst, a.dst_span_vecs);
+  const int64_t chunks = by_chunk ? plan.chunks : p.in_place ? 1 : split_blocks(kOopVec, kOopTpb, split, row_vecs,
+                                                                                      a.misaligned != 0);
   a.chunks = static_cast<uint32_t>(chunks);
   // one dispatch holds fewer than 2^32 work-items: split the spans over
   // several launches when the cache is larger than that
@@ -1413,8 +1409,12 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
     const dim3 grid(static_cast<uint32_t>(blocks));
     if (p.in_place)
       hipLaunchKernelGGL((realign_inplace_kernel<kInVec, kInTpb, kInNt>), grid, block, 0, stream, a);
+    else if (split == 64)
+      hipLaunchKernelGGL((realign_oop_kernel<kOopVec, kOopTpb, 64, kOopNt>), grid, block, 0, stream, a);
+    else if (split == 512)
+      hipLaunchKernelGGL((realign_oop_kernel<kOopVec, kOopTpb, 512, kOopNt>), grid, block, 0, stream, a);
     else
-      hipLaunchKernelGGL((realign_oop_kernel<kOopVec, kOopTpb, kOopSplit, kOopNt>), grid, block, 0, stream, a);
+      hipLaunchKernelGGL((realign_oop_kernel<kOopVec, kOopTpb, 1024, kOopNt>), grid, block, 0, stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (nspans == 0) break;

@@ -328,3 +328,23 @@ def test_inplace_chunks_split_over_launches(monkeypatch):
     for name, items in (("many_edges", 256 * 150), ("many_d128", 256 * 40)):
         monkeypatch.setenv("SPECDEC_MAX_LAUNCH_ITEMS", str(items))
         _full_check(run_gpu(INPLACE_CASES[name], seed=2, variant="inplace", tokens="inplace"))
+
+
+# Out of place, the pieces of a workgroup lie 64, 512 or 1024 vectors apart by
+# the cache's and the spans' size (192 MB; 16384 vectors), with spans that start
+# on and off the boundaries of their groups and end at their edges.
+OOP_CASES = {
+    "split64": _inplace_case(129, [123, 122, 1, 63, 64], D=8, H=3),
+    "split64_d24": _inplace_case(50, [44, 40, 3], D=24, H=5),
+    "split512": _inplace_case(640, [634, 600, 10, 513], D=128, H=300, L=1),
+    "split1024": _inplace_case(16400, [16394, 16000, 50, 8192], D=8, H=100, L=2),
+    "split1024_d128": _inplace_case(1040, [1034, 1000, 100, 1030], D=128, H=100),
+}
+
+
+@pytest.mark.parametrize("cap", [0, 3])
+@pytest.mark.parametrize("name", sorted(OOP_CASES))
+def test_oop_piece_distances(name, cap):
+    w = OOP_CASES[name]
+    r = run_gpu(w, seed=1, variant="oop", tokens="oop", dst_cap=w.W_in + w.extra_cap + cap if cap else w.W_in + 1)
+    _full_check(r)

@@ -7,24 +7,21 @@
 //                   the row maximum and the sum of exp((x - max) / T) of each
 //                   chunk (online: a thread rescales its sum when its maximum
 //                   grows), stored per chunk.
-//   sample_accept   one workgroup per sequence: merges the chunk statistics
+//   sample_finish   one workgroup per (sequence, chunk of V/64 logits, at
+//                   least 2048).  Each merges the sequence's chunk statistics
 //                   into the normalisers of p_r = softmax(target_r / T) and
-//                   q_r = softmax(draft_r / T) (one wave per row), accepts
-//                   draft r iff u_r * q_r(x_r) < p_r(x_r) (wave 0, one lane
-//                   per draft, first rejection by ballot) and stores n_acc and
-//                   the normalisers of the rows the sequence samples from.
-//   sample_mass     one workgroup per (sequence, chunk of V/64 logits, at
-//                   least 2048): the chunk's weights of the distribution to
-//                   sample, the residual max(0, p_j - q_j) after a rejection
-//                   at j (and p_j, its fallback), p_k after k acceptances.
-//                   It also stores the weight total of every tile of 2048
-//                   logits.
-//   sample_pick     one workgroup per sequence: inversion with u_sample,
-//                   coarse to fine: the chunk totals (a prefix over at most
-//                   64 chunks in wave 0), the tile totals of the crossing
-//                   chunk, then one block-wide scan of the crossing tile.
-//                   Workgroup 0 also writes the new width and paddings
-//                   (Eq. (1), Eq. (2)).
+//                   q_r = softmax(draft_r / T), accepts draft r iff
+//                   u_r * q_r(x_r) < p_r(x_r) (one lane per draft, first
+//                   rejection by ballot) and sums its chunk's weights of the
+//                   distribution to sample, the residual max(0, p_j - q_j)
+//                   after a rejection at j (and p_j, its fallback), p_k after
+//                   k acceptances, as the total of every tile of 2048 logits.
+//                   The last workgroup of a sequence to finish draws the token
+//                   by inversion with u_sample, coarse to fine: the chunk
+//                   totals (a prefix over at most 64 chunks in wave 0), the
+//                   tile totals of the crossing chunk, then one block-wide
+//                   scan of the crossing tile.  The last sequence to finish
+//                   writes the new width and paddings (Eq. (1), Eq. (2)).
 //
 // Arithmetic is fp32 with exp2 of (x - max) * log2(e) / T; everything is
 // bandwidth- or latency-bound, no matrix cores.
@@ -38,6 +35,10 @@ constexpr int kStatsThreads = 256;
 constexpr int kGroup = 8;                      // logits per thread per load (16 bytes of bf16 / f16)
 constexpr float kLowest = -3.402823466e38f;    // start of a running maximum (finite, so -inf logits give 0)
 constexpr int kTile = 2048;                     // logits per sub-chunk total (one pick tile)
+// Groups per thread in flight in the row statistics: one 16-byte load of 2048
+// threads a CU is 32 KB, too little for HBM's latency (B = 64, k = 4, V = 151936,
+// bf16, 175 MB: 31.9 us before, 29.7 with four).
+constexpr int kAhead = 4;
 
 // 2^x with the hardware instruction (about 1 ulp; results below the normal
 // range flush to 0, i.e. probabilities below 2^-126 of the row maximum's).
@@ -55,19 +56,21 @@ __device__ __forceinline__ float widen(const char* row, int64_t v) {
   }
 }
 
-// Logits [8g, 8g + 8) of a row (clipped to V; missing ones are -inf), with one
-// 16-byte load per four fp32 or eight 16-bit logits when the group is aligned.
+// A whole aligned group of logits [8g, 8g + 8) of a row, as it lies in memory:
+// one 16-byte load per four fp32 or eight 16-bit logits.
 template <int DT>
-__device__ __forceinline__ void load_group(const char* row, int64_t g, int64_t V, bool aligned, float (&x)[kGroup]) {
-  const int64_t e0 = g * kGroup;
-  if (aligned && e0 + kGroup <= V) {
+struct RawGroup {
+  uint4 a, b;   // b: the second half of fp32 logits
+  __device__ __forceinline__ void load(const char* row, int64_t g) {
+    const uint4* p = reinterpret_cast<const uint4*>(row + (DT == 0 ? 4 : 2) * g * kGroup);
+    a = p[0];
+    if constexpr (DT == 0) b = p[1];
+  }
+  __device__ __forceinline__ void widen(float (&x)[kGroup]) const {
     if constexpr (DT == 0) {
-      const uint4* p = reinterpret_cast<const uint4*>(row + 4 * e0);
-      const uint4 a = p[0], b = p[1];
       x[0] = __uint_as_float(a.x); x[1] = __uint_as_float(a.y); x[2] = __uint_as_float(a.z); x[3] = __uint_as_float(a.w);
       x[4] = __uint_as_float(b.x); x[5] = __uint_as_float(b.y); x[6] = __uint_as_float(b.z); x[7] = __uint_as_float(b.w);
     } else {
-      const uint4 a = *reinterpret_cast<const uint4*>(row + 2 * e0);
       const uint32_t w[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -80,6 +83,17 @@ __device__ __forceinline__ void load_group(const char* row, int64_t g, int64_t V
         }
       }
     }
+  }
+};
+
+// Logits [8g, 8g + 8) of a row, clipped to V (missing ones are -inf).
+template <int DT>
+__device__ __forceinline__ void load_group(const char* row, int64_t g, int64_t V, bool aligned, float (&x)[kGroup]) {
+  const int64_t e0 = g * kGroup;
+  if (aligned && e0 + kGroup <= V) {
+    RawGroup<DT> q;
+    q.load(row, g);
+    q.widen(x);
     return;
   }
 #pragma unroll
@@ -105,9 +119,10 @@ struct SampleArgs {
   int32_t* pad_out;
   int32_t* w_new;
   float2* partial;           // [B*(2k+1)][chunks]: (max, sum of exp2((x - max) * c))
-  float4* norms;             // [B]: (max, 1/sum) of the target and draft rows each sequence samples from
-  float2* mass;              // [B][mchunks][tiles]: (residual weight, target weight) of each tile
-  int2* last;                // [B][mchunks]: last index of positive residual / target weight
+  uint32_t* batch_count;     // sequences that have drawn their token
+  uint32_t* seq_count;       // [B * kCountStride]: finished workgroups of each sequence
+  uint64_t* mass;            // [B][mchunks][tiles]: (residual weight, target weight) of each tile, as two floats
+  uint64_t* last;            // [B][mchunks]: last index of positive residual / target weight, as two int32
   int64_t mchunk_elems;      // logits per mass chunk (a multiple of kGroup, or V)
   int32_t mchunks;           // mass chunks per row (<= 64)
   int32_t tiles;             // tiles of kTile logits per mass chunk
@@ -115,6 +130,33 @@ struct SampleArgs {
   int64_t chunk_elems;       // a multiple of kGroup, or V (one chunk)
   int32_t chunks;
 };
+
+constexpr int kCountStride = 4;   // words from one sequence's count to the next
+
+// Scratch that one workgroup of a launch hands to another of the same launch:
+// agent-scope accesses, which write through to and read from the memory that
+// all XCDs see.  A workgroup waits for its own stores and then counts itself
+// done; whoever counts last sees them all.  The count is relaxed: a
+// releasing one would write back the XCD's whole L2 (19 ns for each workgroup,
+// one after the other).
+template <typename T>
+__device__ __forceinline__ void put(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T get(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// True in every thread of the last of `total` workgroups to call this with
+// `count` (zero before the launch); `flag` is a word of LDS.
+__device__ __forceinline__ bool counted_last(uint32_t* count, uint32_t total, int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's put()s have arrived
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *flag = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1u;
+  __syncthreads();
+  return *flag != 0;
+}
 
 // Row rho < B*(k+1) is target row rho; the rest are draft rows.
 template <int DT>
@@ -136,15 +178,17 @@ __global__ __launch_bounds__(kStatsThreads) void sample_stats_kernel(SampleArgs 
   __shared__ float wm[kStatsThreads / 64], ws[kStatsThreads / 64];
   const int64_t rho = blockIdx.x / a.chunks;
   const int64_t chunk = blockIdx.x - rho * a.chunks;
+  if (threadIdx.x == 0 && chunk == 0) {   // the counts of the launch that follows
+    if (rho == 0) *a.batch_count = 0u;
+    if (rho < a.B) a.seq_count[rho * kCountStride] = 0u;
+  }
   const char* row = stats_row<DT>(a, rho);
   const bool aligned = row_aligned(row, eb);
   const int64_t beg = chunk * a.chunk_elems;
   int64_t end = beg + a.chunk_elems;
   if (end > a.V) end = a.V;
   float m = kLowest, s = 0.0f;
-  for (int64_t g = beg / kGroup + threadIdx.x; g * kGroup < end; g += kStatsThreads) {
-    float x[kGroup];
-    load_group<DT>(row, g, end, aligned, x);
+  auto take = [&](const float (&x)[kGroup]) {
     float gm = x[0];
 #pragma unroll
     for (int e = 1; e < kGroup; ++e) gm = fmaxf(gm, x[e]);
@@ -154,6 +198,25 @@ __global__ __launch_bounds__(kStatsThreads) void sample_stats_kernel(SampleArgs 
     }
 #pragma unroll
     for (int e = 0; e < kGroup; ++e) s += ex2((x[e] - m) * a.c);
+  };
+  int64_t g = beg / kGroup + threadIdx.x;
+  // kAhead whole aligned groups in flight at a time, taken in order
+  if (aligned)
+    for (; (g + (kAhead - 1) * kStatsThreads) * kGroup + kGroup <= end; g += kAhead * kStatsThreads) {
+      RawGroup<DT> q[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) q[u].load(row, g + u * kStatsThreads);
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        float x[kGroup];
+        q[u].widen(x);
+        take(x);
+      }
+    }
+  for (; g * kGroup < end; g += kStatsThreads) {
+    float x[kGroup];
+    load_group<DT>(row, g, end, aligned, x);
+    take(x);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) merge(m, s, __shfl_xor(m, off), __shfl_xor(s, off), a.c);
@@ -170,23 +233,6 @@ __global__ __launch_bounds__(kStatsThreads) void sample_stats_kernel(SampleArgs 
   }
 }
 
-// Normaliser (max, sum) of one logit row from its chunk statistics, by one
-// wave: lane q loads chunk q (all loads in flight at once; at most 64
-// chunks), then a shuffle tree merges them.  Every kernel that needs a row's
-// normaliser uses this, so they all get the same bits.
-__device__ __forceinline__ float2 row_norm(const SampleArgs& a, int64_t rho) {
-  const int lane = threadIdx.x & 63;
-  float M = kLowest, S = 0.0f;
-  if (lane < a.chunks) {
-    const float2 p = a.partial[rho * a.chunks + lane];
-    M = p.x;
-    S = p.y;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) merge(M, S, __shfl_xor(M, off), __shfl_xor(S, off), a.c);
-  return make_float2(M, S);
-}
-
 // Row of slot t of sequence i: slot r <= k is target row r, slot k+1+r
 // draft row r.
 __device__ __forceinline__ int64_t slot_row(const SampleArgs& a, int i, int t) {
@@ -195,14 +241,24 @@ __device__ __forceinline__ int64_t slot_row(const SampleArgs& a, int i, int t) {
                 : static_cast<int64_t>(a.B) * (k + 1) + static_cast<int64_t>(i) * k + (t - k - 1);
 }
 
-// Normalisers of all 2k+1 slots of sequence i into LDS, one wave per slot.
+// Normalisers (max, sum) of all 2k+1 slots of sequence i into LDS, a group of
+// kLanes lanes per slot: lane q loads chunk q's statistics (at most kLanes
+// chunks), then a shuffle tree merges them.
+template <int kLanes>
 __device__ __forceinline__ void row_norms(const SampleArgs& a, int i, float* rowM, float* rowS) {
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int t = wave; t < 2 * a.k + 1; t += nw) {
-    const float2 n = row_norm(a, slot_row(a, i, t));
-    if ((threadIdx.x & 63) == 0) {
-      rowM[t] = n.x;
-      rowS[t] = n.y;
+  const int grp = threadIdx.x / kLanes, lane = threadIdx.x & (kLanes - 1);
+  for (int t = grp; t < 2 * a.k + 1; t += kStatsThreads / kLanes) {
+    float M = kLowest, S = 0.0f;
+    if (lane < a.chunks) {
+      const float2 p = a.partial[slot_row(a, i, t) * a.chunks + lane];
+      M = p.x;
+      S = p.y;
+    }
+#pragma unroll
+    for (int off = kLanes / 2; off > 0; off >>= 1) merge(M, S, __shfl_xor(M, off), __shfl_xor(S, off), a.c);
+    if (lane == 0) {
+      rowM[t] = M;
+      rowS[t] = S;
     }
   }
 }
@@ -299,53 +355,37 @@ struct SampleRows {
   }
 };
 
-constexpr int kAcceptThreads = 256;
-constexpr int kMassThreads = 256;               // kMassThreads * kGroup == kTile: one tile per iteration
-constexpr int kPickThreads = 256;
-static_assert(kMassThreads * kGroup == kTile && kPickThreads * kGroup == kTile, "a tile is one group per thread");
+constexpr int kFinishThreads = kStatsThreads;
+static_assert(kFinishThreads * kGroup == kTile, "a tile is one group per thread");
 constexpr int kMaxTiles = 64;                   // tiles per chunk (V <= 64 * 64 * kTile)
-constexpr int64_t kMassTarget = 2048;           // mass workgroups the chunking aims for
+constexpr int64_t kMassTarget = 2048;           // workgroups the chunking aims for
 
-// One workgroup per sequence: the normalisers of its 2k+1 rows (one wave per
-// row), the acceptance tests (wave 0), then n_acc and the normalisers of the
-// rows the sequence samples from.
-template <int DT>
-__global__ __launch_bounds__(kAcceptThreads) void sample_accept_kernel(SampleArgs a) {
-  __shared__ float rowM[2 * (64 + 1)], rowS[2 * (64 + 1)];
-  const int i = blockIdx.x;
-  const int k = a.k;
-  DraftLogits dl{0.0f, 0.0f, 0.0f, false};
-  if (threadIdx.x < 64) dl = draft_logit_pair<DT>(a, i, true);
-  row_norms(a, i, rowM, rowS);
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int j = accepted_count(a, dl, rowM, rowS);
-    if (threadIdx.x == 0) {
-      a.n_acc[i] = j;
-      a.norms[i] = make_float4(rowM[j], 1.0f / rowS[j], j < k ? rowM[k + 1 + j] : 0.0f,
-                               j < k ? 1.0f / rowS[k + 1 + j] : 0.0f);
-    }
-  }
+__device__ __forceinline__ uint64_t pack(float x, float y) {
+  return __builtin_bit_cast(uint32_t, x) | static_cast<uint64_t>(__builtin_bit_cast(uint32_t, y)) << 32;
+}
+__device__ __forceinline__ uint64_t pack(int32_t x, int32_t y) {
+  return static_cast<uint32_t>(x) | static_cast<uint64_t>(static_cast<uint32_t>(y)) << 32;
+}
+__device__ __forceinline__ float2 unpack_f(uint64_t v) {
+  return make_float2(__uint_as_float(static_cast<uint32_t>(v)), __uint_as_float(static_cast<uint32_t>(v >> 32)));
+}
+__device__ __forceinline__ int2 unpack_i(uint64_t v) {
+  return make_int2(static_cast<int32_t>(v), static_cast<int32_t>(v >> 32));
 }
 
-// One workgroup per (sequence, chunk): tile by tile, the total residual and
-// target weight of each kTile logits of the chunk, and the last index of
-// positive weight of each over the chunk.
+// One chunk of a sequence, tile by tile: the total residual and target weight
+// of each kTile logits, and the last index of positive weight of each over
+// the chunk.
 template <int DT>
-__global__ __launch_bounds__(kMassThreads) void sample_mass_kernel(SampleArgs a) {
-  __shared__ float2 tsum[kMaxTiles][kMassThreads / 64];
-  __shared__ int32_t redi[2][kMassThreads / 64];
-  const int i = static_cast<int>(blockIdx.x / a.mchunks);
-  const int64_t chunk = blockIdx.x - static_cast<int64_t>(i) * a.mchunks;
-  SampleRows<DT> rows;
-  rows.init(a, i, a.n_acc[i], a.norms[i]);
+__device__ void chunk_mass(const SampleArgs& a, const SampleRows<DT>& rows, uint32_t slot, int64_t chunk,
+                           float2 (*tsum)[kFinishThreads / 64], int32_t (*redi)[kFinishThreads / 64]) {
   const int64_t beg = chunk * a.mchunk_elems;
   int64_t end = beg + a.mchunk_elems;
   if (end > a.V) end = a.V;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int32_t lr = -1, lp = -1;
   int t = 0;
-  for (int64_t g = beg / kGroup + threadIdx.x; (g - threadIdx.x) * kGroup < end; g += kMassThreads, ++t) {
+  for (int64_t g = beg / kGroup + threadIdx.x; (g - threadIdx.x) * kGroup < end; g += kFinishThreads, ++t) {
     float sr = 0.0f, sp = 0.0f;
     if (g * kGroup < end) {
       float wr[kGroup], wp[kGroup];
@@ -377,25 +417,25 @@ __global__ __launch_bounds__(kMassThreads) void sample_mass_kernel(SampleArgs a)
   }
   __syncthreads();
   // tile totals in wave order (fixed), one thread per tile
-  for (int tt = threadIdx.x; tt < t; tt += kMassThreads) {
+  for (int tt = threadIdx.x; tt < a.tiles; tt += kFinishThreads) {
     float r = 0.0f, q = 0.0f;
+    if (tt < t) {
 #pragma unroll
-    for (int w = 0; w < kMassThreads / 64; ++w) {
-      r += tsum[tt][w].x;
-      q += tsum[tt][w].y;
+      for (int w = 0; w < kFinishThreads / 64; ++w) {
+        r += tsum[tt][w].x;
+        q += tsum[tt][w].y;
+      }
     }
-    a.mass[(static_cast<int64_t>(blockIdx.x)) * a.tiles + tt] = make_float2(r, q);
+    put(a.mass + static_cast<int64_t>(slot) * a.tiles + tt, pack(r, q));
   }
-  for (int tt = t + threadIdx.x; tt < a.tiles; tt += kMassThreads)
-    a.mass[(static_cast<int64_t>(blockIdx.x)) * a.tiles + tt] = make_float2(0.0f, 0.0f);
   if (threadIdx.x == 0) {
     int32_t mr = -1, mp = -1;
 #pragma unroll
-    for (int w = 0; w < kMassThreads / 64; ++w) {
+    for (int w = 0; w < kFinishThreads / 64; ++w) {
       mr = redi[0][w] > mr ? redi[0][w] : mr;
       mp = redi[1][w] > mp ? redi[1][w] : mp;
     }
-    a.last[blockIdx.x] = make_int2(mr, mp);
+    put(a.last + slot, pack(mr, mp));
   }
 }
 
@@ -444,15 +484,15 @@ __device__ __forceinline__ int first_crossing(float v, int n, float base, float 
   return cs;
 }
 
-// New width and paddings (Eq. (1), Eq. (2)) from the accepted counts, by one
-// workgroup of kPickThreads.
+// New width and paddings (Eq. (1), Eq. (2)) from the accepted counts, by the
+// last workgroup of the launch.
 __device__ void width_and_pads(const SampleArgs& a, int32_t* red) {
   const int32_t L = a.W_in - (a.k + 1);
   int32_t local = 0;
-  for (int i = threadIdx.x; i < a.B; i += kPickThreads) {
+  for (int i = threadIdx.x; i < a.B; i += kFinishThreads) {
     const int32_t p = a.pad_in[i];
     if (p >= 0 && p <= L) {
-      const int32_t len = (L - p) + a.n_acc[i] + 1;
+      const int32_t len = (L - p) + get(a.n_acc + i) + 1;
       local = len > local ? len : local;
     } else if (a.dev_status) {
       atomicOr(a.dev_status, kBadPadIn);
@@ -468,41 +508,84 @@ __device__ void width_and_pads(const SampleArgs& a, int32_t* red) {
   __syncthreads();
   int32_t w = red[0];
 #pragma unroll
-  for (int q = 1; q < kPickThreads / 64; ++q) w = red[q] > w ? red[q] : w;
-  for (int i = threadIdx.x; i < a.B; i += kPickThreads) {
+  for (int q = 1; q < kFinishThreads / 64; ++q) w = red[q] > w ? red[q] : w;
+  for (int i = threadIdx.x; i < a.B; i += kFinishThreads) {
     const int32_t p = a.pad_in[i];
-    a.pad_out[i] = (p >= 0 && p <= L) ? w - ((L - p) + a.n_acc[i] + 1) : -1;
+    a.pad_out[i] = (p >= 0 && p <= L) ? w - ((L - p) + get(a.n_acc + i) + 1) : -1;
   }
   if (threadIdx.x == 0) a.w_new[0] = w;
 }
 
-// One workgroup per sequence: inversion with u_sample, coarse to fine: the
-// chunk totals (wave 0, at most 64 chunks), the tile totals of the crossing
-// chunk (wave 0), then one block-wide scan of the crossing tile.  A residual
+// One workgroup per (sequence, chunk), see the top of the file.  A residual
 // with no mass falls back to p_j; where rounding leaves no crossing, the last
-// index of positive weight seen is taken.  Workgroup 0 also writes the new
-// width and paddings.
+// index of positive weight seen is taken.
+//
+// The accept tests are repeated by every workgroup of a sequence (its chunk
+// statistics are a few hundred bytes), and the drawing is left to the last one
+// to finish, because a launch costs more than either: accept, mass and pick
+// kernels took 4.9 + 11.1 + 8.1 us at B = 64, k = 4, V = 151936 (bf16) and 4.0 +
+// 3.6 + 7.1 at B = 2, k = 5, V = 32000; this one takes 21.6 and 10 to 12, and two
+// launches fewer leave the host, which bounds the small calls, 6 us (whole
+// call 20 -> 15).
 template <int DT>
-__global__ __launch_bounds__(kPickThreads) void sample_pick_kernel(SampleArgs a) {
-  __shared__ float red[kPickThreads / 64];
-  __shared__ int32_t redl[kPickThreads / 64];
-  __shared__ int32_t s_tile, s_first, s_pick, s_fallback, s_use_res;
+__global__ __launch_bounds__(kFinishThreads) void sample_finish_kernel(SampleArgs a) {
+  __shared__ float rowM[2 * (64 + 1)], rowS[2 * (64 + 1)];
+  __shared__ float2 tsum[kMaxTiles][kFinishThreads / 64];
+  __shared__ int32_t redi[2][kFinishThreads / 64];
+  __shared__ float red[kFinishThreads / 64];
+  __shared__ int32_t redl[kFinishThreads / 64];
+  __shared__ int32_t s_tile, s_first, s_pick, s_fallback, s_use_res, s_acc;
   __shared__ float s_excl, s_target;
-  const int i = blockIdx.x;
+  __shared__ int last_here;
+  // the first B workgroups count what each sequence accepts; the others are
+  // (sequence, chunk) ones
+  const bool counts = static_cast<int>(blockIdx.x) < a.B;
+  const uint32_t slot = blockIdx.x - static_cast<uint32_t>(a.B);
+  const int i = counts ? static_cast<int>(blockIdx.x) : static_cast<int>(slot / a.mchunks);
+  const int64_t chunk = counts ? 0 : slot - static_cast<int64_t>(i) * a.mchunks;
   const int k = a.k;
-  const int j = a.n_acc[i];
-  if (blockIdx.x == 0) width_and_pads(a, redl);
+  DraftLogits dl{0.0f, 0.0f, 0.0f, false};
+  if (threadIdx.x < 64) dl = draft_logit_pair<DT>(a, i, counts);
+  if (a.chunks <= 16) row_norms<16>(a, i, rowM, rowS);
+  else row_norms<64>(a, i, rowM, rowS);
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int r = accepted_count(a, dl, rowM, rowS);
+    if (threadIdx.x == 0) s_acc = r;
+  }
+  __syncthreads();
+  const int j = s_acc;
+  if (counts) {
+    if (threadIdx.x == 0) put(a.n_acc + i, j);
+    if (counted_last(a.batch_count, static_cast<uint32_t>(a.B), &last_here)) width_and_pads(a, redl);
+    return;
+  }
+  SampleRows<DT> rows;
+  rows.init(a, i, j, make_float4(rowM[j], 1.0f / rowS[j], j < k ? rowM[k + 1 + j] : 0.0f, j < k ? 1.0f / rowS[k + 1 + j] : 0.0f));
+  chunk_mass<DT>(a, rows, slot, chunk, tsum, redi);
+  if (!counted_last(a.seq_count + static_cast<int64_t>(i) * kCountStride, static_cast<uint32_t>(a.mchunks), &last_here)) return;
   if (threadIdx.x < 64) {
     const int c = threadIdx.x;
-    const int64_t wg0 = static_cast<int64_t>(i) * a.mchunks;  // mass workgroups of this sequence
+    const int64_t wg0 = static_cast<int64_t>(i) * a.mchunks;  // workgroups of this sequence
+    // the chunk's tile totals; the first few stay in registers
+    constexpr int kHeld = 4;
+    float2 held[kHeld];
+#pragma unroll
+    for (int tt = 0; tt < kHeld; ++tt)
+      held[tt] = c < a.mchunks && tt < a.tiles ? unpack_f(get(a.mass + (wg0 + c) * a.tiles + tt)) : make_float2(0.0f, 0.0f);
     float cr = 0.0f, cp = 0.0f;
+#pragma unroll
+    for (int tt = 0; tt < kHeld; ++tt) {
+      cr += held[tt].x;
+      cp += held[tt].y;
+    }
     if (c < a.mchunks)
-      for (int tt = 0; tt < a.tiles; ++tt) {
-        const float2 m = a.mass[(wg0 + c) * a.tiles + tt];
+      for (int tt = kHeld; tt < a.tiles; ++tt) {
+        const float2 m = unpack_f(get(a.mass + (wg0 + c) * a.tiles + tt));
         cr += m.x;
         cp += m.y;
       }
-    const int2 l = c < a.mchunks ? a.last[wg0 + c] : make_int2(-1, -1);
+    const int2 l = c < a.mchunks ? unpack_i(get(a.last + wg0 + c)) : make_int2(-1, -1);
     float rtot = cr;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) rtot += __shfl_xor(rtot, off);
@@ -532,8 +615,18 @@ __global__ __launch_bounds__(kPickThreads) void sample_pick_kernel(SampleArgs a)
     int ts = -1;
     float excl_tile = 0.0f;
     if (cs >= 0) {
-      const float2 m = c < a.tiles ? a.mass[(wg0 + cs) * a.tiles + c] : make_float2(0.0f, 0.0f);
-      ts = first_crossing(use_res ? m.x : m.y, a.tiles, excl_chunk, target, &excl_tile);
+      float tile_mass = 0.0f;   // of tile c of chunk cs
+      if (a.tiles <= kHeld) {
+#pragma unroll
+        for (int tt = 0; tt < kHeld; ++tt) {
+          const float m = __shfl(use_res ? held[tt].x : held[tt].y, cs);
+          if (c == tt) tile_mass = m;
+        }
+      } else if (c < a.tiles) {
+        const float2 m = unpack_f(get(a.mass + (wg0 + cs) * a.tiles + c));
+        tile_mass = use_res ? m.x : m.y;
+      }
+      ts = first_crossing(tile_mass, a.tiles, excl_chunk, target, &excl_tile);
     }
     if (c == 0) {
       s_tile = cs >= 0 && ts >= 0 ? cs * a.tiles + ts : -1;   // tile index within the row
@@ -547,8 +640,6 @@ __global__ __launch_bounds__(kPickThreads) void sample_pick_kernel(SampleArgs a)
   __syncthreads();
   const int tile = s_tile;
   if (tile >= 0) {
-    SampleRows<DT> rows;
-    rows.init(a, i, j, a.norms[i]);
     const bool use_res = s_use_res != 0;
     const float target = s_target;
     const int cs = tile / a.tiles, ts = tile - cs * a.tiles;
@@ -571,7 +662,7 @@ __global__ __launch_bounds__(kPickThreads) void sample_pick_kernel(SampleArgs a)
       if (w[e] > 0.0f) lastg = static_cast<int32_t>(g * kGroup + e);
     }
     float tt = 0.0f;
-    const float incl = s_excl + block_inclusive_scan<kPickThreads>(gs, red, &tt);
+    const float incl = s_excl + block_inclusive_scan<kFinishThreads>(gs, red, &tt);
     if (threadIdx.x == 0) s_first = 0x7FFFFFFF;
     __syncthreads();
     if (incl > target) atomicMin(&s_first, static_cast<int32_t>(threadIdx.x));
@@ -598,7 +689,7 @@ __global__ __launch_bounds__(kPickThreads) void sample_pick_kernel(SampleArgs a)
     if (threadIdx.x == 0 && s_pick < 0) {
       int32_t m = -1;
 #pragma unroll
-      for (int q = 0; q < kPickThreads / 64; ++q) m = redl[q] > m ? redl[q] : m;
+      for (int q = 0; q < kFinishThreads / 64; ++q) m = redl[q] > m ? redl[q] : m;
       s_pick = m;
     }
   }
@@ -627,7 +718,7 @@ int64_t sample_chunks(int64_t rows, int64_t V) {
 }
 
 int64_t sample_mass_chunk_elems(int64_t B, int64_t V) {
-  // at most 64 chunks per row (one lane each in the pick kernel), at least
+  // at most 64 chunks per row (one lane each where the token is drawn), at least
   // one tile each, and about kMassTarget workgroups in all: 8 of 256 threads
   // per CU, so the whole grid is resident at once (at B = 64, V = 151936,
   // 64 chunks per row took two rounds of workgroups: 13.4 us against 11.5)
@@ -666,12 +757,13 @@ static hipError_t sample_args(const SampleLaunch& p, SampleArgs& a) {
   a.mchunks = static_cast<int32_t>((p.V + a.mchunk_elems - 1) / a.mchunk_elems);
   a.tiles = static_cast<int32_t>((a.mchunk_elems + kTile - 1) / kTile);
   if (a.tiles > kMaxTiles || a.mchunks > 64) return hipErrorInvalidValue;
+  a.batch_count = static_cast<uint32_t*>(p.workspace);
   char* ws = static_cast<char*>(p.workspace) + kWsHeaderBytes;
-  a.norms = reinterpret_cast<float4*>(ws);
-  ws += static_cast<int64_t>(p.B) * 16;
+  a.seq_count = reinterpret_cast<uint32_t*>(ws);
+  ws += static_cast<int64_t>(p.B) * kCountStride * 4;
   a.partial = reinterpret_cast<float2*>(ws);
-  a.last = reinterpret_cast<int2*>(ws + rows * a.chunks * 8);
-  a.mass = reinterpret_cast<float2*>(ws + (rows * a.chunks + static_cast<int64_t>(p.B) * a.mchunks) * 8);
+  a.last = reinterpret_cast<uint64_t*>(ws + rows * a.chunks * 8);
+  a.mass = reinterpret_cast<uint64_t*>(ws + (rows * a.chunks + static_cast<int64_t>(p.B) * a.mchunks) * 8);
   return hipSuccess;
 }
 
@@ -693,26 +785,11 @@ hipError_t launch_sample_finish(const SampleLaunch& p, hipStream_t stream) {
   SampleArgs a{};
   hipError_t e = sample_args(p, a);
   if (e != hipSuccess) return e;
-  const dim3 seqs(static_cast<uint32_t>(p.B));
+  const dim3 grid(static_cast<uint32_t>(static_cast<int64_t>(p.B) * (a.mchunks + 1)));
   switch (p.dtype) {
-    case 0: hipLaunchKernelGGL(sample_accept_kernel<0>, seqs, dim3(kAcceptThreads), 0, stream, a); break;
-    case 1: hipLaunchKernelGGL(sample_accept_kernel<1>, seqs, dim3(kAcceptThreads), 0, stream, a); break;
-    default: hipLaunchKernelGGL(sample_accept_kernel<2>, seqs, dim3(kAcceptThreads), 0, stream, a); break;
-  }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const dim3 mgrid(static_cast<uint32_t>(static_cast<int64_t>(p.B) * a.mchunks));
-  switch (p.dtype) {
-    case 0: hipLaunchKernelGGL(sample_mass_kernel<0>, mgrid, dim3(kMassThreads), 0, stream, a); break;
-    case 1: hipLaunchKernelGGL(sample_mass_kernel<1>, mgrid, dim3(kMassThreads), 0, stream, a); break;
-    default: hipLaunchKernelGGL(sample_mass_kernel<2>, mgrid, dim3(kMassThreads), 0, stream, a); break;
-  }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  switch (p.dtype) {
-    case 0: hipLaunchKernelGGL(sample_pick_kernel<0>, seqs, dim3(kPickThreads), 0, stream, a); break;
-    case 1: hipLaunchKernelGGL(sample_pick_kernel<1>, seqs, dim3(kPickThreads), 0, stream, a); break;
-    default: hipLaunchKernelGGL(sample_pick_kernel<2>, seqs, dim3(kPickThreads), 0, stream, a); break;
+    case 0: hipLaunchKernelGGL(sample_finish_kernel<0>, grid, dim3(kFinishThreads), 0, stream, a); break;
+    case 1: hipLaunchKernelGGL(sample_finish_kernel<1>, grid, dim3(kFinishThreads), 0, stream, a); break;
+    default: hipLaunchKernelGGL(sample_finish_kernel<2>, grid, dim3(kFinishThreads), 0, stream, a); break;
   }
   return hipGetLastError();
 }

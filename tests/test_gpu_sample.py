@@ -311,3 +311,36 @@ def test_step_sample_equals_split_calls(sd, variant):
         assert np.array_equal(a[1][name], b[1][name]), name
     for x, y in zip(a[2:], b[2:]):
         assert np.array_equal(x, y)
+
+
+def test_repeated_calls_on_one_workspace(sd):
+    """The drawing is left to whichever workgroup of a sequence finishes last,
+    counted in the workspace: calls of several shapes in turn on one workspace
+    (counts of one call, statistics of another and garbage in the same places)
+    give the same outputs every time, and the oracle's."""
+    rng = np.random.default_rng(77)
+    shapes = [(1, 0, 5, "f32"), (2, 64, 9000, "bf16"), (40, 4, 30001, "f16"), (700, 1, 2049, "bf16"), (3, 2, 140000, "bf16")]
+    ws = torch.full((max(sd.sample_workspace_bytes(B, k, V) for B, k, V, _ in shapes) // 8 + 1,), -1, dtype=torch.int64,
+                    device="cuda")
+    calls = []
+    for B, k, V, dt in shapes:
+        tl, dl, draft, ua, us = _make(rng, B, k, V, dt, 1.0)
+        pad = rng.integers(0, 20, size=B).astype(np.int32)
+        i32 = dict(dtype=torch.int32, device="cuda")
+        out = [torch.empty(s, **i32) for s in ((B, k + 1), (B,), (B,), (B,), (1,), (1,))]
+        out[-1].zero_()
+        dev = [torch.as_tensor(x).cuda() for x in (tl, dl, draft, pad, ua, us)]
+        calls.append((dev, out, (tl, dl, dt, draft, pad, ua, us, 1.0, 21 + k)))
+    first = {}
+    for turn in range(6):
+        for n, (dev, out, host) in enumerate(calls):
+            sd.specdec_verify_sample(*dev, 1.0, host[-1], *out[:5], ws, out[5])
+            got = [t.clone() for t in out]
+            if turn:
+                assert all(torch.equal(a, b) for a, b in zip(got, first[n])), f"call {n} differs in turn {turn}"
+            first.setdefault(n, got)
+    for n, (_, _, host) in enumerate(calls):
+        names = ("tokens", "n_acc", "bonus", "pad_out", "w_new", "status")
+        got = {m: t.cpu().numpy() for m, t in zip(names, first[n])}
+        got.update(w_new=int(got["w_new"][0]), status=int(got["status"][0]))
+        check_against_oracle(*host, got)

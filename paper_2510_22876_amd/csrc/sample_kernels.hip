@@ -241,27 +241,44 @@ __device__ __forceinline__ int64_t slot_row(const SampleArgs& a, int i, int t) {
                 : static_cast<int64_t>(a.B) * (k + 1) + static_cast<int64_t>(i) * k + (t - k - 1);
 }
 
-// Normalisers (max, sum) of all 2k+1 slots of sequence i into LDS, a group of
+// Normalisers (max, sum) of the 2k+1 slots of sequence i into LDS, a group of
 // kLanes lanes per slot: lane q loads chunk q's statistics (at most kLanes
-// chunks), then a shuffle tree merges them.
+// chunks), then a shuffle tree merges them.  Four slots a group are loaded at
+// once, the first four before the caller's other loads.
 template <int kLanes>
-__device__ __forceinline__ void row_norms(const SampleArgs& a, int i, float* rowM, float* rowS) {
-  const int grp = threadIdx.x / kLanes, lane = threadIdx.x & (kLanes - 1);
-  for (int t = grp; t < 2 * a.k + 1; t += kStatsThreads / kLanes) {
-    float M = kLowest, S = 0.0f;
-    if (lane < a.chunks) {
-      const float2 p = a.partial[slot_row(a, i, t) * a.chunks + lane];
-      M = p.x;
-      S = p.y;
-    }
+struct RowNorms {
+  static constexpr int kGroups = kStatsThreads / kLanes, kSlots = 4;
+  float2 p[kSlots];
+  __device__ __forceinline__ void load(const SampleArgs& a, int i, int t0) {
+    const int grp = threadIdx.x / kLanes, lane = threadIdx.x & (kLanes - 1);
 #pragma unroll
-    for (int off = kLanes / 2; off > 0; off >>= 1) merge(M, S, __shfl_xor(M, off), __shfl_xor(S, off), a.c);
-    if (lane == 0) {
-      rowM[t] = M;
-      rowS[t] = S;
+    for (int u = 0; u < kSlots; ++u) {
+      const int t = t0 + u * kGroups + grp;
+      p[u] = make_float2(kLowest, 0.0f);
+      if (t < 2 * a.k + 1 && lane < a.chunks) p[u] = a.partial[slot_row(a, i, t) * a.chunks + lane];
     }
   }
-}
+  __device__ __forceinline__ void merge_all(const SampleArgs& a, int i, float* rowM, float* rowS) {
+    const int grp = threadIdx.x / kLanes, lane = threadIdx.x & (kLanes - 1);
+    for (int t0 = 0;;) {
+#pragma unroll
+      for (int u = 0; u < kSlots; ++u) {
+        if (t0 + u * kGroups >= 2 * a.k + 1) break;   // block-uniform
+        float M = p[u].x, S = p[u].y;
+#pragma unroll
+        for (int off = kLanes / 2; off > 0; off >>= 1) merge(M, S, __shfl_xor(M, off), __shfl_xor(S, off), a.c);
+        const int t = t0 + u * kGroups + grp;
+        if (lane == 0 && t < 2 * a.k + 1) {
+          rowM[t] = M;
+          rowS[t] = S;
+        }
+      }
+      t0 += kSlots * kGroups;
+      if (t0 >= 2 * a.k + 1) return;
+      load(a, i, t0);
+    }
+  }
+};
 
 // Acceptance tests of sequence i, one lane of wave 0 per draft: draft r is
 // accepted iff u_r * q_r(x_r) < p_r(x_r).  draft_logit_pair loads the two
@@ -339,13 +356,12 @@ struct SampleRows {
   // residual weights (0 when there is no residual) and target weights of a group
   __device__ __forceinline__ void weights(int64_t g, int64_t end, float c, float (&wr)[kGroup],
                                           float (&wp)[kGroup]) const {
-    float xt[kGroup];
+    float xt[kGroup], xd[kGroup];
     load_group<DT>(trow, g, end, ta, xt);
+    if (residual) load_group<DT>(drow, g, end, da, xd);
 #pragma unroll
     for (int e = 0; e < kGroup; ++e) wp[e] = ex2((xt[e] - tM) * c);
     if (residual) {
-      float xd[kGroup];
-      load_group<DT>(drow, g, end, da, xd);
 #pragma unroll
       for (int e = 0; e < kGroup; ++e) wr[e] = fmaxf(wp[e] * tinv - ex2((xd[e] - dM) * c) * dinv, 0.0f);
     } else {
@@ -545,9 +561,17 @@ __global__ __launch_bounds__(kFinishThreads) void sample_finish_kernel(SampleArg
   const int64_t chunk = counts ? 0 : slot - static_cast<int64_t>(i) * a.mchunks;
   const int k = a.k;
   DraftLogits dl{0.0f, 0.0f, 0.0f, false};
-  if (threadIdx.x < 64) dl = draft_logit_pair<DT>(a, i, counts);
-  if (a.chunks <= 16) row_norms<16>(a, i, rowM, rowS);
-  else row_norms<64>(a, i, rowM, rowS);
+  if (a.chunks <= 16) {
+    RowNorms<16> n;
+    n.load(a, i, 0);
+    if (threadIdx.x < 64) dl = draft_logit_pair<DT>(a, i, counts);
+    n.merge_all(a, i, rowM, rowS);
+  } else {
+    RowNorms<64> n;
+    n.load(a, i, 0);
+    if (threadIdx.x < 64) dl = draft_logit_pair<DT>(a, i, counts);
+    n.merge_all(a, i, rowM, rowS);
+  }
   __syncthreads();
   if (threadIdx.x < 64) {
     const int r = accepted_count(a, dl, rowM, rowS);

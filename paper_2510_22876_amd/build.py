@@ -1,7 +1,9 @@
 """Build libspecdec.so for gfx950 with hipcc (in-tree, next to this file).
 
 Usage: ``python -m paper_2510_22876_amd.build``.  Every HIP source is compiled
-with packed-FP32 instructions disabled (``-packed-fp32-ops``).
+with packed-FP32 instructions disabled (``-packed-fp32-ops``).  The native
+argument marshalling of the Python binding (``_marshal.so``, host code against
+torch's headers) is built beside it.
 """
 from __future__ import annotations
 
@@ -14,6 +16,7 @@ PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libspecdec.so"
+MARSHAL = PKG / "_marshal.so"
 ARCH = "gfx950"
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
@@ -47,6 +50,26 @@ def build(verbose: bool = False, defines=(), out: Path = LIB, build_dir: Path | 
     return Path(out)
 
 
+def build_marshal(verbose: bool = False) -> Path:
+    """Compile the extension module ``_marshal`` (host code only)."""
+    import sysconfig
+
+    import torch
+    root = Path(torch.__file__).resolve().parent
+    tmp = MARSHAL.with_suffix(".so.tmp")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{ROOT / 'include'}", f"-isystem{root / 'include'}", f"-I{sysconfig.get_paths()['include']}",
+           str(CSRC / "python" / "marshal.cpp"), f"-L{root / 'lib'}", "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-o", str(tmp)]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
+
+
 if __name__ == "__main__":
     build(verbose="-v" in sys.argv)
+    build_marshal(verbose="-v" in sys.argv)
     print(LIB)

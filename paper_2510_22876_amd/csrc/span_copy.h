@@ -130,14 +130,13 @@ inline int64_t split_blocks(int64_t vecs, bool misaligned = false) {
 //     memory's access pattern;
 //   16384 spans of 60 KB 340 / 306 / 299, 67584 of 59 KB 798 / 745 / 877, 16384
 //     of 120 KB 623 / 590 / 587: 512;
-//   16384 spans of 0.9 MB 3492 / 2819 / 2786, 2048 of 0.9 MB 381 / 367 / 362: long
-//     padded spans, where a group of 32 KB rounds up little (16384 of 260 KB
-//     1185 / 1129 / 1131).  Where rows end as they come (a write-back of 16 rows
-//     of 64..4096 columns) it leaves more workgroups empty: 989 / 1016 at 512 /
-//     1024.
+//   16384 spans of 0.9 MB 3492 / 2819 / 2786, 2048 of 0.9 MB 381 / 367 / 362, but
+//     16384 of 260 KB 1185 / 1128 / 1132: 1024 for long padded spans.  Where rows
+//     end as they come (a write-back of 16 rows of 64..4096 columns) it leaves
+//     more workgroups empty: 989 / 1016 at 512 / 1024.
 inline int split_distance(int64_t spans, int64_t vecs, bool padded) {
   if (spans * vecs * 16 <= (192ll << 20)) return 64;
-  return padded && vecs >= 16 * 1024 ? 1024 : 512;
+  return padded && vecs >= 32 * 1024 ? 1024 : 512;
 }
 
 // Output spans are tiled in groups of kPieces*kSplit vectors.  When a span

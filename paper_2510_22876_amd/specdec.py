@@ -4,6 +4,11 @@ Argument marshalling only: torch tensors are passed as device pointers, the
 stream is torch's current HIP stream, and every step of the path runs in the
 library's HIP kernels.  Importing this module loads the library and raises if
 it has not been built; there is no fallback.
+
+The calls of a decoding loop are marshalled by the extension module
+``_marshal`` (csrc/python/marshal.cpp), which makes the same checks natively
+and hands anything it does not take as it stands back to the Python code here;
+where the module is not built, the Python code does it all.
 """
 from __future__ import annotations
 
@@ -116,6 +121,22 @@ lib = _load()
 LIB_PATH = str(_LIB_PATH)
 
 
+def _load_native():
+    """The native marshalling, calling the functions of ``lib``; None when it
+    is not built for this interpreter and torch."""
+    try:
+        from paper_2510_22876_amd import _marshal
+        device, raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    except (ImportError, AttributeError):
+        return None
+    _marshal.connect(device, raw_stream,
+                     {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in EXPORTED})
+    return _marshal
+
+
+_native = _load_native()
+
+
 def _check(code: int) -> None:
     if code != OK:
         raise SpecdecError(code, lib.specdec_last_error().decode())
@@ -152,6 +173,11 @@ def _stream(stream) -> int | None:
     if stream is None:
         return torch.cuda.current_stream().cuda_stream or None
     return stream if isinstance(stream, int) else stream.cuda_stream
+
+
+def _raw(stream):
+    """A stream argument for the native marshalling: None or an integer."""
+    return getattr(stream, "cuda_stream", stream)
 
 
 def kv_desc(t: torch.Tensor) -> KV:
@@ -205,6 +231,11 @@ def _check_verify(logits, draft, pad_in, tokens, n_acc, bonus, pad_out, w_new, w
 
 def specdec_verify_greedy(logits, draft, pad_in, W_in: int, tokens, n_acc, bonus, pad_out, w_new,
                           workspace, dev_status=None, stream=None) -> None:
+    if _native is not None:
+        r = _native.verify_greedy(logits, draft, pad_in, W_in, tokens, n_acc, bonus, pad_out, w_new, workspace,
+                                  dev_status, _raw(stream))
+        if r is not NotImplemented:
+            return _check(r)
     B, kp1, V = logits.shape
     _check_verify(logits, draft, pad_in, tokens, n_acc, bonus, pad_out, w_new, workspace, dev_status)
     _check(lib.specdec_verify_greedy(
@@ -227,6 +258,11 @@ def specdec_verify_sample(logits, draft_logits, draft, pad_in, u_accept, u_sampl
                           tokens, n_acc, bonus, pad_out, w_new, workspace, dev_status=None, stream=None) -> None:
     """Stochastic (T > 0) verification by speculative sampling with the
     caller's uniforms (u_accept [B][k], u_sample [B], float32)."""
+    if _native is not None:
+        r = _native.verify_sample(logits, draft_logits, draft, pad_in, u_accept, u_sample, temperature, W_in, tokens,
+                                  n_acc, bonus, pad_out, w_new, workspace, dev_status, _raw(stream))
+        if r is not NotImplemented:
+            return _check(r)
     if logits.dim() != 3 or logits.dtype not in DTYPE_OF or not logits.is_cuda or not logits.is_contiguous():
         raise ValueError("logits must be a contiguous device tensor [B][k+1][V] of float32/bfloat16/float16")
     B, kp1, V = logits.shape
@@ -317,11 +353,23 @@ def _greedy_step(noalloc, logits, draft, pad_in, W_in, src, dst, tokens, n_acc, 
     return (lib.specdec_step_noalloc if noalloc else lib.specdec_step), head + ws + tail, host
 
 
+def _step_result(r):
+    """L' of a natively marshalled step that asked for it: (status, L')."""
+    if type(r) is tuple:
+        return r[1]
+    return _check(r)
+
+
 def specdec_step(logits, draft, pad_in, W_in: int, src, dst, tokens, n_acc, bonus, pad_out, w_new,
                  pos, mask, workspace, dev_status=None, sync_w_new: bool = False, stream=None,
                  s_in=None, s_out=None, pad_id: int = 0):
     """The fused step (with the token row S when ``s_in`` / ``s_out`` are
     given); returns L' as a Python int when ``sync_w_new``."""
+    if _native is not None and workspace is not None:
+        r = _native.step(logits, draft, pad_in, W_in, src, dst, tokens, n_acc, bonus, pad_out, w_new, pos, mask,
+                         workspace, dev_status, bool(sync_w_new), _raw(stream), s_in, s_out, pad_id)
+        if r is not NotImplemented:
+            return _step_result(r)
     fn, args, host = _greedy_step(False, logits, draft, pad_in, W_in, src, dst, tokens, n_acc, bonus, pad_out, w_new,
                                   pos, mask, workspace, dev_status, sync_w_new, stream, s_in, s_out, pad_id)
     _check(fn(*args))
@@ -333,6 +381,11 @@ def specdec_step_noalloc(logits, draft, pad_in, W_in: int, src, dst, tokens, n_a
                          s_in=None, s_out=None, pad_id: int = 0):
     """``specdec_step`` on the library's own scratch (no workspace argument);
     returns L' as a Python int when ``sync_w_new``."""
+    if _native is not None:
+        r = _native.step(logits, draft, pad_in, W_in, src, dst, tokens, n_acc, bonus, pad_out, w_new, pos, mask,
+                         None, dev_status, bool(sync_w_new), _raw(stream), s_in, s_out, pad_id)
+        if r is not NotImplemented:
+            return _step_result(r)
     fn, args, host = _greedy_step(True, logits, draft, pad_in, W_in, src, dst, tokens, n_acc, bonus, pad_out, w_new,
                                   pos, mask, None, dev_status, sync_w_new, stream, s_in, s_out, pad_id)
     _check(fn(*args))
@@ -381,6 +434,11 @@ def specdec_gather_batch(pool, pool_tok, lens, slots, Lb: int, batch, pads, batc
     """EXSpec's GetBatch: rows ``slots`` of the pool gathered into ``batch``,
     left-padded to width ``Lb`` (with token rows, paddings and, when given,
     position ids / mask over [0, Lb + k + 1))."""
+    if _native is not None:
+        r = _native.gather_batch(pool, pool_tok, lens, slots, Lb, batch, pads, batch_tok, pos, mask, k, pad_id,
+                                 dev_status, _raw(stream))
+        if r is not NotImplemented:
+            return _check(r)
     pl = kv_desc(pool)
     bt = kv_desc(batch)
     B = bt.B
@@ -408,6 +466,11 @@ def specdec_scatter_accepted(batch, pads, tokens, n_acc, slots, Lb: int, pool, p
     """EXSpec's write-back: each row's unpadded cache up to its accepted
     entries returns to its pool slot (whole, or only the new entries with
     ``mode=WRITEBACK_APPEND``); the slot's token list and length grow."""
+    if _native is not None:
+        r = _native.scatter_accepted(batch, pads, tokens, n_acc, slots, Lb, pool, pool_tok, lens, batch_tok, mode,
+                                     dev_status, _raw(stream))
+        if r is not NotImplemented:
+            return _check(r)
     bt = kv_desc(batch)
     pl = kv_desc(pool)
     B = bt.B
@@ -491,6 +554,12 @@ def specdec_step_sample(logits, draft_logits, draft, pad_in, u_accept, u_sample,
                         sync_w_new: bool = False, stream=None, s_in=None, s_out=None, pad_id: int = 0):
     """The fused step with stochastic verification (speculative sampling with
     the caller's uniforms); returns L' as a Python int when ``sync_w_new``."""
+    if _native is not None:
+        r = _native.step_sample(logits, draft_logits, draft, pad_in, u_accept, u_sample, temperature, W_in, src, dst,
+                                tokens, n_acc, bonus, pad_out, w_new, pos, mask, workspace, dev_status,
+                                bool(sync_w_new), _raw(stream), s_in, s_out, pad_id)
+        if r is not NotImplemented:
+            return _step_result(r)
     B, kp1, V = logits.shape
     k = kp1 - 1
     if logits.dtype not in DTYPE_OF or not logits.is_cuda or not logits.is_contiguous():
@@ -552,6 +621,10 @@ def varlen_desc(t: torch.Tensor) -> Varlen:
 def specdec_varlen_rollback(src, dst, cu_in, n_acc, k: int, max_len: int, cu_out, pos=None, dev_status=None,
                             stream=None) -> None:
     """Family B rollback: compaction of a flat cache by cumulative lengths."""
+    if _native is not None:
+        r = _native.varlen_rollback(src, dst, cu_in, n_acc, k, max_len, cu_out, pos, dev_status, _raw(stream))
+        if r is not NotImplemented:
+            return _check(r)
     s, d = varlen_desc(src), varlen_desc(dst)
     B = cu_in.numel() - 1
     _req("cu_in", cu_in, (B + 1,), torch.int32)

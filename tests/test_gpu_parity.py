@@ -331,14 +331,14 @@ def test_inplace_chunks_split_over_launches(monkeypatch):
 
 
 # Out of place, the pieces of a workgroup lie 64, 512 or 1024 vectors apart by
-# the cache's and the spans' size (192 MB; 16384 vectors), with spans that start
+# the cache's and the spans' size (192 MB; 32768 vectors), with spans that start
 # on and off the boundaries of their groups and end at their edges.
 OOP_CASES = {
     "split64": _inplace_case(129, [123, 122, 1, 63, 64], D=8, H=3),
     "split64_d24": _inplace_case(50, [44, 40, 3], D=24, H=5),
     "split512": _inplace_case(640, [634, 600, 10, 513], D=128, H=300, L=1),
-    "split1024": _inplace_case(16400, [16394, 16000, 50, 8192], D=8, H=100, L=2),
-    "split1024_d128": _inplace_case(1040, [1034, 1000, 100, 1030], D=128, H=100),
+    "split1024": _inplace_case(32780, [32774, 32000, 50, 8192], D=8, H=50, L=2),
+    "split1024_d128": _inplace_case(2050, [2044, 2000, 100, 2040], D=128, H=50),
 }
 
 

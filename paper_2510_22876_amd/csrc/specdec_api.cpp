@@ -461,19 +461,14 @@ specdec_status_t check_step_disjoint(const StepInputs& v, int32_t B, int32_t k, 
   return check_disjoint(in, sizeof(in) / sizeof(in[0]), out, sizeof(out) / sizeof(out[0]));
 }
 
-// The realignment launch of a fused step (cache, position ids / mask, token
-// row), then the optional host copy of the new width.
-specdec_status_t step_realign(int32_t k, int32_t W_in, const specdec_kv_t* src, const specdec_kv_t* dst,
-                              bool in_place, const int32_t* pad_in, const int32_t* tokens, const int32_t* n_acc,
-                              const int32_t* pad_out, const int32_t* w_new, int64_t* pos, uint8_t* mask,
-                              int64_t pm_cap, const int32_t* s_in, int64_t s_in_stride, int32_t* s_out,
-                              int64_t s_out_stride, int32_t pad_id, uint32_t* dev_status, int32_t* w_new_host,
-                              hipStream_t st, uint32_t* clear_words = nullptr, uint32_t clear_count = 0,
-                              const int32_t* order = nullptr) {
+// The realignment of a fused step (cache, position ids / mask, token row).
+specdec::RealignLaunch step_realign_launch(int32_t k, int32_t W_in, const specdec_kv_t* src, const specdec_kv_t* dst,
+                                           bool in_place, const int32_t* pad_in, const int32_t* tokens,
+                                           const int32_t* n_acc, const int32_t* pad_out, const int32_t* w_new,
+                                           int64_t* pos, uint8_t* mask, int64_t pm_cap, const int32_t* s_in,
+                                           int64_t s_in_stride, int32_t* s_out, int64_t s_out_stride, int32_t pad_id,
+                                           uint32_t* dev_status) {
   specdec::RealignLaunch rp{};
-  rp.clear_words = clear_words;
-  rp.clear_count = clear_count;
-  rp.order = order;
   rp.src = src->data;
   rp.dst = dst->data;
   rp.src_cap = src->cap;
@@ -499,7 +494,14 @@ specdec_status_t step_realign(int32_t k, int32_t W_in, const specdec_kv_t* src, 
   rp.s_out_stride = s_out_stride;
   rp.tokens = tokens;
   rp.pad_id = pad_id;
-  hipError_t e = timed(SPECDEC_KERNEL_REALIGN, st, [&] { return specdec::launch_realign(rp, st); });
+  return rp;
+}
+
+// The last launch of a fused step (`launch`), then the optional host copy of
+// the new width.
+template <typename F>
+specdec_status_t step_finish(hipStream_t st, const int32_t* w_new, int32_t* w_new_host, F&& launch) {
+  hipError_t e = timed(SPECDEC_KERNEL_REALIGN, st, launch);
   if (e != hipSuccess) return hip_fail(e, "realign launch");
   if (w_new_host) {
     e = hipMemcpyAsync(w_new_host, w_new, sizeof(int32_t), hipMemcpyDeviceToHost, st);
@@ -750,20 +752,31 @@ specdec_status_t step_greedy(const void* logits, int32_t dtype, const int32_t* d
   hipStream_t st = static_cast<hipStream_t>(stream);
   specdec::VerifyLaunch vp{logits, dtype, draft, pad_in, B, k, V, W_in, tokens, n_acc,
                            bonus, pad_out, w_new, workspace, dev_status};
-  // where a walk realigns the cache in place, the merge launch also writes
-  // the order it takes the rows in
-  vp.write_order = in_place && !fused_counts && specdec::inplace_plan(src->L, B, src->H, src->D, W_in).chunks == 0;
-  const int32_t* order =
-      vp.write_order ? reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + specdec::order_offset(B, k, V))
-                     : nullptr;
-  hipError_t e = fused_counts ? timed(SPECDEC_KERNEL_VERIFY, st, [&] {
-    return timed(SPECDEC_KERNEL_VERIFY_SCAN, st, [&] { return specdec::launch_verify_fused(vp, fused_counts, st); });
-  })
-                              : verify_launches(vp, st);
+  specdec::RealignLaunch rp = step_realign_launch(k, W_in, src, dst, in_place, pad_in, tokens, n_acc, pad_out, w_new, pos,
+                                                  mask, pm_cap, s_in, s_in_stride, s_out, s_out_stride, pad_id, dev_status);
+  hipError_t e = hipSuccess;
+  if (fused_counts) {
+    rp.clear_words = fused_counts;
+    rp.clear_count = static_cast<uint32_t>(B) + 1u;
+    e = timed(SPECDEC_KERNEL_VERIFY, st, [&] {
+      return timed(SPECDEC_KERNEL_VERIFY_SCAN, st, [&] { return specdec::launch_verify_fused(vp, fused_counts, st); });
+    });
+  } else if (specdec::small_step_fits(vp, rp)) {
+    e = timed(SPECDEC_KERNEL_VERIFY, st, [&] {
+      return timed(SPECDEC_KERNEL_VERIFY_SCAN, st, [&] { return specdec::launch_verify_scan(vp, st); });
+    });
+    if (e != hipSuccess) return hip_fail(e, "verify launch");
+    return step_finish(st, w_new, w_new_host, [&] { return specdec::launch_small_step(vp, rp, st); });
+  } else {
+    // where a walk realigns the cache in place, the merge launch also writes
+    // the order it takes the rows in
+    vp.write_order = in_place && specdec::inplace_plan(src->L, B, src->H, src->D, W_in).chunks == 0;
+    if (vp.write_order)
+      rp.order = reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + specdec::order_offset(B, k, V));
+    e = verify_launches(vp, st);
+  }
   if (e != hipSuccess) return hip_fail(e, "verify launch");
-  return step_realign(k, W_in, src, dst, in_place, pad_in, tokens, n_acc, pad_out, w_new, pos, mask, pm_cap, s_in,
-                      s_in_stride, s_out, s_out_stride, pad_id, dev_status, w_new_host, st, fused_counts,
-                      fused_counts ? static_cast<uint32_t>(B) + 1u : 0u, order);
+  return step_finish(st, w_new, w_new_host, [&] { return specdec::launch_realign(rp, st); });
 }
 
 }  // namespace
@@ -914,8 +927,10 @@ specdec_status_t specdec_step_sample(const void* logits, const void* draft_logit
                            B, k, V, W_in, tokens, n_acc, bonus, pad_out, w_new, workspace, dev_status};
   hipError_t e = sample_launches(sp, st);
   if (e != hipSuccess) return hip_fail(e, "stochastic verify launch");
-  return step_realign(k, W_in, src, dst, in_place, pad_in, tokens, n_acc, pad_out, w_new, pos, mask, pm_cap, s_in,
-                      s_in_stride, s_out, s_out_stride, pad_id, dev_status, w_new_host, st);
+  const specdec::RealignLaunch rp =
+      step_realign_launch(k, W_in, src, dst, in_place, pad_in, tokens, n_acc, pad_out, w_new, pos, mask, pm_cap, s_in,
+                          s_in_stride, s_out, s_out_stride, pad_id, dev_status);
+  return step_finish(st, w_new, w_new_host, [&] { return specdec::launch_realign(rp, st); });
 }
 
 specdec_status_t specdec_gather_batch(const specdec_kv_t* pool, const int32_t* pool_tok, int64_t pool_tok_stride,

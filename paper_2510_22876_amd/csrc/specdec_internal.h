@@ -230,6 +230,11 @@ constexpr int64_t kMaxFusedVerifyRowBytes = 16 * 1024;
 bool verify_fused_fits(int64_t B, int64_t k, int64_t V, int dtype);
 hipError_t launch_verify_fused(const VerifyLaunch& p, uint32_t* counts, hipStream_t stream);
 hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream);
+// A small step after the vocabulary scan: the merge and the realignment in one
+// launch (greedy steps that small_step_fits accepts; their workspace holds the
+// scan's partial maxima).
+bool small_step_fits(const VerifyLaunch& v, const RealignLaunch& p);
+hipError_t launch_small_step(const VerifyLaunch& v, const RealignLaunch& p, hipStream_t stream);
 hipError_t launch_posmask(const PosmaskLaunch& p, hipStream_t stream);
 // Token row only (RealignLaunch's cache fields are ignored).
 hipError_t launch_tokens(const RealignLaunch& p, hipStream_t stream);

@@ -580,6 +580,18 @@ __global__ __launch_bounds__(kFusedThreads) void verify_fused_kernel(FusedVerify
 #define SPECDEC_INPLACE_NT 3
 #endif
 
+constexpr int kOopVec = SPECDEC_OOP_VEC, kOopTpb = SPECDEC_OOP_TPB, kOopNt = SPECDEC_OOP_NT;
+constexpr int kInVec = SPECDEC_INPLACE_VEC, kInTpb = SPECDEC_INPLACE_TPB, kInNt = SPECDEC_INPLACE_NT;
+static_assert(kOopTpb % 64 == 0 && kInTpb % 64 == 0, "workgroups are whole wavefronts");
+constexpr int kSmallTpb = 256;   // threads of a small step's merged launch
+// A small step: workgroups that move the cache, and bytes that they merge in
+// all (out of place, in place).  Steps in us, three launches / two: 1024
+// workgroups of 3 KB, in place 20.0 / 15.9; 2048 of 24 KB 33.2 / 32.9; 4096 of
+// 12 KB 55.8 / 55.2; 8192 of 3 KB 97.7 / 94.4, of 14 KB 45.2 / 54.3.  Out of
+// place 2560 of 6 KB 15.7 / 14.9, 3072 of 6 KB 15.3 / 15.7, 5120 of 1.5 KB 19.0 /
+// 17.5, 6144 of 0.8 KB 21.2 / 20.4.
+constexpr int64_t kSmallMaxBlocks = 8192, kSmallMaxMergedOop = 16 << 20, kSmallMaxMergedInPlace = 52 << 20;
+
 struct RealignArgs {
   const u32x4* src;
   u32x4* dst;
@@ -614,18 +626,17 @@ struct RealignArgs {
   uint32_t clear_count;
   const int32_t* order;                  // in place: verification's order table (NULL: the cache's order)
   uint32_t span_rows;                    // spans per row: L * 2 * H
-  uint32_t slots;                        // in place by chunks: spans * chunks
+  uint32_t slots;                        // in place by chunks, and in a small step: spans * chunks
 };
 
 struct RowGeom {
   int32_t pad_in, pad_out, len, w;
 };
 
-__device__ __forceinline__ uint32_t row_geometry(const RealignArgs& a, int row, RowGeom& g) {
+// Geometry of a row with padding p, n accepted drafts and the new width w;
+// returns the error bits (0 = valid).
+__device__ __forceinline__ uint32_t geometry_of(const RealignArgs& a, int32_t w, int32_t p, int32_t n, RowGeom& g) {
   const int32_t L = a.W_in - (a.k + 1);
-  const int32_t w = load_invariant(a.w_new);
-  const int32_t p = load_invariant(a.pad_in + row);
-  const int32_t n = load_invariant(a.n_acc + row);
   uint32_t err = 0u;
   if (p < 0 || p > L) err |= kBadPadIn;
   if (n < 0 || n > a.k) err |= kBadAccept;
@@ -639,15 +650,15 @@ __device__ __forceinline__ uint32_t row_geometry(const RealignArgs& a, int row, 
   return 0u;
 }
 
-// Position ids and mask for 4*kTpb columns of one row.
+__device__ __forceinline__ uint32_t row_geometry(const RealignArgs& a, int row, RowGeom& g) {
+  return geometry_of(a, load_invariant(a.w_new), load_invariant(a.pad_in + row), load_invariant(a.n_acc + row), g);
+}
+
+// Position ids and mask for 4*kTpb columns (the cb-th) of one row with new
+// padding po, in a batch of new width w.
 template <int kTpb>
-__device__ void posmask_block(uint32_t blk, int64_t* pos, uint8_t* mask, const int32_t* pad_out,
-                              const int32_t* w_new, int32_t k, int64_t pm_cap, uint32_t col_blocks,
-                              uint32_t* dev_status) {
-  const uint32_t row = blk / col_blocks;
-  const uint32_t cb = blk - row * col_blocks;
-  const int32_t w = load_invariant(w_new);
-  const int32_t po = load_invariant(pad_out + row);
+__device__ __forceinline__ void posmask_row(uint32_t row, uint32_t cb, int64_t* pos, uint8_t* mask, int32_t po, int32_t w,
+                                            int32_t k, int64_t pm_cap, uint32_t* dev_status) {
   const int64_t width = static_cast<int64_t>(w) + k + 1;
   if (w < 0 || po < 0 || po > w || width > pm_cap) {
     if (cb == 0 && threadIdx.x == 0 && dev_status) atomicOr(dev_status, kBadPadOut);
@@ -657,6 +668,15 @@ __device__ void posmask_block(uint32_t blk, int64_t* pos, uint8_t* mask, const i
                      width);
 }
 
+template <int kTpb>
+__device__ void posmask_block(uint32_t blk, int64_t* pos, uint8_t* mask, const int32_t* pad_out,
+                              const int32_t* w_new, int32_t k, int64_t pm_cap, uint32_t col_blocks,
+                              uint32_t* dev_status) {
+  const uint32_t row = blk / col_blocks;
+  posmask_row<kTpb>(row, blk - row * col_blocks, pos, mask, load_invariant(pad_out + row), load_invariant(w_new), k,
+                    pm_cap, dev_status);
+}
+
 // Token row S of one sequence (Alg. 1, phase 3): the c_i + 1 tokens of the
 // row (its cached tokens and the pending token) move from column pad_in to
 // pad_out, the accepted drafts and the bonus token (the predictions
@@ -664,29 +684,23 @@ __device__ void posmask_block(uint32_t blk, int64_t* pos, uint8_t* mask, const i
 // new row is L' + 1 wide.  Out of place a workgroup writes 4*kTpb columns of
 // one row; in place one workgroup walks the whole row in the direction of its
 // shift and writes the padding and the appended tokens after a barrier.
+// (w, p, n: the new width, the row's padding and accepted count; tk: its
+// predictions.)
 template <int kTpb>
-__device__ void token_block(const RealignArgs& a, uint32_t blk) {
-  const uint32_t row = blk / a.tok_col_blocks;
-  const uint32_t cb = blk - row * a.tok_col_blocks;
-  const int32_t L = a.W_in - (a.k + 1);
-  const int32_t w = load_invariant(a.w_new);
-  const int32_t p = load_invariant(a.pad_in + row);
-  const int32_t n = load_invariant(a.n_acc + row);
-  uint32_t err = 0u;
-  if (p < 0 || p > L) err |= kBadPadIn;
-  if (n < 0 || n > a.k) err |= kBadAccept;
-  const int32_t c = L - p;
-  if (!err && (w < 1 || w > a.W_in || c + n + 1 > w)) err |= kBadWidth;
+__device__ void token_row(const RealignArgs& a, uint32_t row, uint32_t cb, int32_t w, int32_t p, int32_t n,
+                          const int32_t* tk) {
+  RowGeom g;
+  const uint32_t err = geometry_of(a, w, p, n, g);
   if (err) {
     if (cb == 0 && threadIdx.x == 0 && a.dev_status) atomicOr(a.dev_status, err);
     return;
   }
-  const int64_t po = static_cast<int64_t>(w) - (c + n + 1);   // new padding
+  const int32_t c = a.W_in - (a.k + 1) - p;
+  const int64_t po = g.pad_out;                                 // new padding
   const int64_t keep_end = po + c + 1;                          // end of the moved tokens
   const int64_t width = static_cast<int64_t>(w) + 1;
   const int32_t* src = a.s_in + static_cast<int64_t>(row) * a.s_in_stride;
   int32_t* dst = a.s_out + static_cast<int64_t>(row) * a.s_out_stride;
-  const int32_t* tk = a.tokens + static_cast<int64_t>(row) * (a.k + 1);
   if (a.s_in != a.s_out) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -728,6 +742,13 @@ __device__ void token_block(const RealignArgs& a, uint32_t blk) {
   }
   for (int64_t j = threadIdx.x; j < po; j += kTpb) dst[j] = a.pad_id;
   for (int64_t j = keep_end + threadIdx.x; j < width; j += kTpb) dst[j] = tk[j - keep_end];
+}
+
+template <int kTpb>
+__device__ void token_block(const RealignArgs& a, uint32_t blk) {
+  const uint32_t row = blk / a.tok_col_blocks;
+  token_row<kTpb>(a, row, blk - row * a.tok_col_blocks, load_invariant(a.w_new), load_invariant(a.pad_in + row),
+                  load_invariant(a.n_acc + row), a.tokens + static_cast<int64_t>(row) * (a.k + 1));
 }
 
 template <int kTpb>
@@ -978,23 +999,8 @@ __device__ __forceinline__ uint32_t spread(uint32_t i, uint32_t slots) {
 // a chunk is shorter than 2 d (a shift of many columns), one workgroup walks
 // the span instead.
 template <int kVec, int kTpb, int kNt, bool kMany>
-__global__ __launch_bounds__(kTpb) void realign_chunk_kernel(RealignArgs a) {
-  if (blockIdx.x < a.extra_blocks) {
-    extra_block<kTpb>(a, blockIdx.x);
-    return;
-  }
+__device__ __forceinline__ void move_chunk(const RealignArgs& a, uint32_t span, int c, const RowGeom& geo) {
   constexpr int kChunk = kTpb * kVec;
-  const uint32_t g = spread(a.span_base + (blockIdx.x - a.extra_blocks), a.slots);   // span * chunks + chunk
-  const uint32_t span = kMany ? g / a.chunks : g;
-  const int c = kMany ? static_cast<int>(g - span * a.chunks) : 0;
-  const uint32_t row = (span / static_cast<uint32_t>(a.H)) % static_cast<uint32_t>(a.B);
-  RowGeom geo;
-  const uint32_t err = row_geometry(a, static_cast<int>(row), geo);
-  if (err) {
-    if (c == 0 && span == row * static_cast<uint32_t>(a.H) && threadIdx.x == 0 && a.dev_status)
-      atomicOr(a.dev_status, err);
-    return;
-  }
   const int64_t vpc = a.vpc;
   const int64_t shift = static_cast<int64_t>(geo.pad_out - geo.pad_in) * vpc;
   if (shift == 0) return;
@@ -1059,6 +1065,26 @@ __global__ __launch_bounds__(kTpb) void realign_chunk_kernel(RealignArgs a) {
   }
 }
 
+template <int kVec, int kTpb, int kNt, bool kMany>
+__global__ __launch_bounds__(kTpb) void realign_chunk_kernel(RealignArgs a) {
+  if (blockIdx.x < a.extra_blocks) {
+    extra_block<kTpb>(a, blockIdx.x);
+    return;
+  }
+  const uint32_t g = spread(a.span_base + (blockIdx.x - a.extra_blocks), a.slots);   // span * chunks + chunk
+  const uint32_t span = kMany ? g / a.chunks : g;
+  const int c = kMany ? static_cast<int>(g - span * a.chunks) : 0;
+  const uint32_t row = (span / static_cast<uint32_t>(a.H)) % static_cast<uint32_t>(a.B);
+  RowGeom geo;
+  const uint32_t err = row_geometry(a, static_cast<int>(row), geo);
+  if (err) {
+    if (c == 0 && span == row * static_cast<uint32_t>(a.H) && threadIdx.x == 0 && a.dev_status)
+      atomicOr(a.dev_status, err);
+    return;
+  }
+  move_chunk<kVec, kTpb, kNt, kMany>(a, span, c, geo);
+}
+
 // Hands the strips that realign_chunk_kernel parked over to the neighbour
 // chunks, one workgroup per span.  For a shift to higher addresses, strip c
 // (the first d vectors of chunk c) goes to the first d vectors of chunk c+1,
@@ -1119,6 +1145,113 @@ __global__ __launch_bounds__(kTpb) void realign_strips_kernel(RealignArgs a, int
   if (shift > 0) zero_vectors<kTpb, kNt>(at, shift);
 }
 
+// ---------------------------------------------------------------------------
+// Small steps: after the vocabulary scan, one launch that merges it and
+// realigns.  Every workgroup merges the partial maxima for itself (a few KB:
+// at most kSmallRows logit rows) and goes on with its share of the
+// realignment, so that the merge is not a launch of its own; workgroup 0 also
+// stores the verification's outputs.  A launch costs such a step more than
+// the repeated merge: the tiny step takes 9.1 us instead of 12.4, two rows of 64
+// to 200 columns on one KV head in place 10.4 instead of 20.1.
+// ---------------------------------------------------------------------------
+constexpr int kSmallRows = kSmallTpb;
+
+struct SmallOutcome {
+  int32_t tok[kSmallRows];    // predictions [B][k+1]
+  int32_t n_acc[kSmallRows], pad_in[kSmallRows], pad_out[kSmallRows];
+  int32_t wmax[kSmallTpb / 64];
+  int32_t w;
+};
+
+// `lanes` threads to a logit row: a power of two, at most 64, rows * lanes <= kSmallTpb.
+__device__ void small_merge(const VerifyArgs& a, int lanes, SmallOutcome& s) {
+  const int t = threadIdx.x, kp1 = a.k + 1, rows = a.B * kp1;
+  const int row = t / lanes, q = t & (lanes - 1);
+  const int i = row / kp1, r = row - i * kp1;
+  const bool leads = row < rows && q == 0;
+  const int32_t drafted = leads && r < a.k ? a.draft[i * a.k + r] : 0;
+  const int32_t p = t < a.B ? a.pad_in[t] : 0;
+  unsigned long long m = 0u;
+  if (row < rows)
+    for (int c = q; c < a.chunks; c += lanes) {
+      const unsigned long long v = a.partial[static_cast<int64_t>(row) * a.chunks + c];
+      m = v > m ? v : m;
+    }
+  for (int off = lanes >> 1; off > 0; off >>= 1) {
+    const unsigned long long o = __shfl_xor(m, off);
+    m = o > m ? o : m;
+  }
+  if (t < a.B) {
+    s.n_acc[t] = a.k;
+    s.pad_in[t] = p;
+  }
+  __syncthreads();
+  if (leads) {
+    const int32_t tok = static_cast<int32_t>(~static_cast<uint32_t>(m & 0xFFFFFFFFull));
+    s.tok[row] = tok;
+    if (r < a.k && drafted != tok) atomicMin(&s.n_acc[i], r);   // the first mismatch
+  }
+  __syncthreads();
+  const int32_t L = a.W_in - kp1;
+  const int32_t len = t < a.B && p >= 0 && p <= L ? (L - p) + s.n_acc[t] + 1 : 0;
+  const int32_t most = wave_max_i32(len);
+  if ((t & 63) == 0) s.wmax[t >> 6] = most;
+  __syncthreads();
+  int32_t w = s.wmax[0];
+#pragma unroll
+  for (int v = 1; v < kSmallTpb / 64; ++v) w = s.wmax[v] > w ? s.wmax[v] : w;
+  const int32_t po = len > 0 ? w - len : -1;
+  if (t < a.B) s.pad_out[t] = po;
+  if (t == 0) s.w = w;
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    if (t < rows) a.tokens[t] = s.tok[t];
+    if (t < a.B) {
+      const int32_t n = s.n_acc[t];
+      a.n_acc[t] = n;
+      a.pad_out[t] = po;
+      if (a.bonus) a.bonus[t] = s.tok[t * kp1 + n];
+      if (len == 0 && a.dev_status) atomicOr(a.dev_status, kBadPadIn);
+    }
+    if (t == 0) a.w_new[0] = w;
+  }
+}
+
+template <bool kInPlace, int kVec>
+__global__ __launch_bounds__(kSmallTpb) void small_step_kernel(VerifyArgs v, RealignArgs a, int lanes) {
+  __shared__ SmallOutcome s;
+  small_merge(v, lanes, s);
+  uint32_t b = blockIdx.x;
+  if (b < a.pm_blocks) {
+    const uint32_t row = b / a.pm_col_blocks;
+    posmask_row<kSmallTpb>(row, b - row * a.pm_col_blocks, a.pos, a.mask, s.pad_out[row], s.w, a.k, a.pm_cap, a.dev_status);
+    return;
+  }
+  b -= a.pm_blocks;
+  if (b < a.tok_blocks) {
+    const uint32_t row = b / a.tok_col_blocks;
+    token_row<kSmallTpb>(a, row, b - row * a.tok_col_blocks, s.w, s.pad_in[row], s.n_acc[row], s.tok + row * (a.k + 1));
+    return;
+  }
+  b = spread(b - a.tok_blocks, a.slots);
+  const uint32_t span = b / a.chunks, sub = b - span * a.chunks;
+  const uint32_t row = (span / static_cast<uint32_t>(a.H)) % static_cast<uint32_t>(a.B);
+  RowGeom g;
+  if (geometry_of(a, s.w, s.pad_in[row], s.n_acc[row], g)) return;   // a bad padding: flagged by workgroup 0
+  if constexpr (kInPlace) {
+    move_chunk<kVec, kSmallTpb, kInNt, false>(a, span, 0, g);
+  } else {
+    // pieces of a whole workgroup, one after the other
+    const int64_t total = static_cast<int64_t>(g.w) * a.vpc;
+    const int64_t base = static_cast<int64_t>(sub) * (kVec * kSmallTpb);
+    if (base >= total) return;
+    split_pieces<kVec, kSmallTpb, kSmallTpb, kOopNt>(a.src + static_cast<int64_t>(span) * a.src_span_vecs,
+                                                     a.dst + static_cast<int64_t>(span) * a.dst_span_vecs, base, total,
+                                                     static_cast<int64_t>(g.pad_out) * a.vpc,
+                                                     static_cast<int64_t>(g.pad_out - g.pad_in) * a.vpc);
+  }
+}
+
 __global__ __launch_bounds__(kThreads) void posmask_kernel(int64_t* pos, uint8_t* mask,
                                                            const int32_t* pad_out, const int32_t* w_new,
                                                            int32_t k, int64_t pm_cap, uint32_t col_blocks,
@@ -1136,9 +1269,6 @@ __global__ __launch_bounds__(kThreads) void zero_kernel(uint4* p16, int64_t n16,
   if (i < ntail) tail[i] = 0;
 }
 
-constexpr int kOopVec = SPECDEC_OOP_VEC, kOopTpb = SPECDEC_OOP_TPB, kOopNt = SPECDEC_OOP_NT;
-constexpr int kInVec = SPECDEC_INPLACE_VEC, kInTpb = SPECDEC_INPLACE_TPB, kInNt = SPECDEC_INPLACE_NT;
-static_assert(kOopTpb % 64 == 0 && kInTpb % 64 == 0, "workgroups are whole wavefronts");
 
 }  // namespace
 
@@ -1420,6 +1550,78 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
     if (nspans == 0) break;
   }
   return hipSuccess;
+}
+
+// Threads to a logit row in the small step's merge, or 0 where the step is
+// not a small one.
+static int small_step_lanes(const VerifyLaunch& v) {
+  const int64_t rows = static_cast<int64_t>(v.B) * (v.k + 1);
+  if (rows > kSmallRows || rows < 1) return 0;
+  int lanes = 1;
+  while (lanes < 64 && rows * lanes * 2 <= kSmallTpb) lanes *= 2;
+  return lanes;
+}
+
+// Vectors a thread of the merged launch moves, and workgroups per span.
+static void small_step_share(const RealignLaunch& p, int* vec, int64_t* blocks) {
+  const int64_t longest = static_cast<int64_t>(p.W_in) * (p.D / 8);
+  if (p.in_place) {
+    *vec = longest <= 4 * kSmallTpb ? 4 : 16;
+    *blocks = 1;
+  } else {
+    *vec = 2;
+    *blocks = (longest + 2 * kSmallTpb - 1) / (2 * kSmallTpb);
+  }
+}
+
+bool small_step_fits(const VerifyLaunch& v, const RealignLaunch& p) {
+  const int64_t nspans = static_cast<int64_t>(p.L) * 2 * p.B * p.H;
+  if (!small_step_lanes(v) || nspans < 1 || p.clear_words || !p.pos) return false;
+  const int64_t longest = static_cast<int64_t>(p.W_in) * (p.D / 8);
+  if (p.in_place && longest > 16 * kSmallTpb) return false;
+  int vec;
+  int64_t blocks;
+  small_step_share(p, &vec, &blocks);
+  blocks *= nspans;
+  const int64_t rows = static_cast<int64_t>(v.B) * (v.k + 1);
+  const int64_t merged = rows * verify_chunks(rows, v.V) * 8;   // bytes each workgroup merges
+  const int64_t cols = static_cast<int64_t>(p.W_in) + p.k + 1;
+  const int64_t extra = 2 * p.B * ((cols + 4 * kSmallTpb - 1) / (4 * kSmallTpb));
+  return blocks <= kSmallMaxBlocks && blocks * merged <= (p.in_place ? kSmallMaxMergedInPlace : kSmallMaxMergedOop) && (blocks + extra) * kSmallTpb <= max_launch_items();
+}
+
+hipError_t launch_small_step(const VerifyLaunch& v, const RealignLaunch& p, hipStream_t stream) {
+  RealignArgs a{};
+  a.src = static_cast<const u32x4*>(p.src);
+  a.dst = static_cast<u32x4*>(p.dst);
+  a.vpc = p.D / 8;
+  a.src_span_vecs = p.src_cap * a.vpc;
+  a.dst_span_vecs = p.dst_cap * a.vpc;
+  a.B = p.B;
+  a.H = p.H;
+  a.k = p.k;
+  a.W_in = p.W_in;
+  a.dev_status = p.dev_status;
+  a.pos = p.pos;
+  a.mask = p.mask;
+  a.pm_cap = p.pm_cap;
+  const int64_t cols = static_cast<int64_t>(p.W_in) + p.k + 1;
+  a.pm_col_blocks = static_cast<uint32_t>((cols + 4 * kSmallTpb - 1) / (4 * kSmallTpb));
+  a.pm_blocks = a.pm_col_blocks * static_cast<uint32_t>(p.B);
+  fill_token_args(a, p, kSmallTpb);
+  a.tok_blocks = a.tok_col_blocks * static_cast<uint32_t>(p.B);
+  int vec;
+  int64_t blocks;
+  small_step_share(p, &vec, &blocks);
+  a.chunks = static_cast<uint32_t>(blocks);
+  a.slots = static_cast<uint32_t>(static_cast<int64_t>(p.L) * 2 * p.B * p.H * blocks);
+  const dim3 grid(a.slots + a.pm_blocks + a.tok_blocks), block(kSmallTpb);
+  const VerifyArgs va = verify_args(v);
+  const int lanes = small_step_lanes(v);
+  if (!p.in_place) hipLaunchKernelGGL((small_step_kernel<false, 2>), grid, block, 0, stream, va, a, lanes);
+  else if (vec == 4) hipLaunchKernelGGL((small_step_kernel<true, 4>), grid, block, 0, stream, va, a, lanes);
+  else hipLaunchKernelGGL((small_step_kernel<true, 16>), grid, block, 0, stream, va, a, lanes);
+  return hipGetLastError();
 }
 
 hipError_t launch_tokens(const RealignLaunch& p, hipStream_t stream) {

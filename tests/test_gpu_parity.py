@@ -314,11 +314,12 @@ INPLACE_CASES = {
 }
 
 
+@pytest.mark.parametrize("api", ["step", "split"])
 @pytest.mark.parametrize("name", sorted(INPLACE_CASES))
-def test_inplace_routes(name):
+def test_inplace_routes(name, api):
     w = INPLACE_CASES[name]
     for seed in (1, 4):
-        r = run_gpu(w, seed=seed, variant="inplace", tokens="inplace")
+        r = run_gpu(w, seed=seed, variant="inplace", api=api, tokens="inplace")
         _full_check(r)
         W = r.out["w_new"]
         assert torch.equal(i16(r.dst[..., W:, :]), i16(r.src[..., W:, :])), "columns beyond the new width were written"
@@ -346,5 +347,50 @@ OOP_CASES = {
 @pytest.mark.parametrize("name", sorted(OOP_CASES))
 def test_oop_piece_distances(name, cap):
     w = OOP_CASES[name]
-    r = run_gpu(w, seed=1, variant="oop", tokens="oop", dst_cap=w.W_in + w.extra_cap + cap if cap else w.W_in + 1)
+    r = run_gpu(w, seed=1, variant="oop", api="split", tokens="oop", dst_cap=w.W_in + w.extra_cap + cap if cap else w.W_in + 1)
     _full_check(r)
+
+
+# Small steps merge the scan in the realignment's workgroups: up to 256 logit
+# rows (a lane group of 1 to 64 threads a row), then the merge is a launch of
+# its own again; spans at the edges of what a workgroup moves (512 vectors out
+# of place; 1024 and 4096 in place).
+@pytest.mark.parametrize("variant", ["oop", "inplace"])
+@pytest.mark.parametrize("B,k,V,W_in,D", [(1, 0, 70000, 513, 8), (2, 1, 40000, 512, 8), (3, 64, 300, 1024, 8),
+                                          (128, 1, 33, 40, 8), (64, 3, 5000, 70, 24), (129, 1, 33, 40, 8),
+                                          (256, 0, 9, 30, 8), (5, 7, 20000, 4096, 8), (7, 4, 9000, 1025, 8)])
+def test_small_steps(B, k, V, W_in, D, variant):
+    rng = np.random.default_rng(B + W_in)
+    ns = rng.integers(0, W_in - k, size=B)
+    ns[rng.integers(B)] = W_in - k - 1
+    w = wl.Workload("small", B=B, k=k, V=V, logit_dtype="bf16", logit_std=2.0, L=1, H=2, D=D, prompt=("list", ns.tolist()),
+                    accept=("uniform",), W_in=W_in, tie_frac=0.1, extra_cap=2)
+    r = run_gpu(w, seed=B, variant=variant, tokens=variant)
+    _full_check(r)
+
+
+@pytest.mark.parametrize("variant", ["oop", "inplace"])
+def test_small_step_bad_padding(variant):
+    """A row with a padding out of range in a small step: flagged, its cache and
+    token row untouched, left out of the width; the others are the oracle's."""
+    from paper_2510_22876_amd import specdec as sd
+    w = _inplace_case(60, [54, 30, 20, 41])
+    pad = np.array([0, 24, 99, 13], np.int32)
+    logits, draft, *_ = wl.logits_and_drafts(w, 1, device="cuda")
+    src = wl.make_kv(w, np.array([0, 24, 34, 13]), 60, 67, 1, device="cuda")
+    before = src.clone()
+    dst = src if variant == "inplace" else torch.full_like(i16(src), SENT_KV).view(torch.bfloat16)
+    o = alloc_outputs(w.B, w.k, w.V, 70)
+    sd.specdec_step(logits, draft, torch.as_tensor(pad, device="cuda"), 60, src, dst, o.tokens, o.n_acc, o.bonus,
+                    o.pad_out, o.w_new, o.pos, o.mask, o.workspace, o.dev_status)
+    torch.cuda.synchronize()
+    good = [0, 1, 3]
+    v = oracle.verify(logits[good].cpu(), w.logit_dtype, draft[good].cpu().numpy(), pad[good], 60)
+    assert int(o.dev_status) == sd.DEV_BAD_PAD_IN | sd.DEV_BAD_PAD_OUT
+    assert int(o.w_new) == v["w_new"] and int(o.pad_out[2]) == -1
+    for name in ("tokens", "n_acc", "bonus", "pad_out"):
+        assert np.array_equal(getattr(o, name).cpu().numpy()[good], v[name]), name
+    exp = oracle.realign_kv(np.ascontiguousarray(bits(before)[:, :, good]), w.k, 60, pad[good], v["n_acc"], v["w_new"])
+    W = v["w_new"]
+    assert np.array_equal(bits(dst)[:, :, good][..., :W, :], exp[..., :W, :])
+    assert torch.equal(i16(dst[:, :, 2]), i16(before[:, :, 2]) if variant == "inplace" else torch.full_like(i16(dst[:, :, 2]), SENT_KV))

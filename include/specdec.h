@@ -105,8 +105,8 @@ const char* specdec_last_error(void);
 /* Bytes of device workspace specdec_verify_greedy / specdec_step need for a
  * batch of B rows, k drafts and a vocabulary of V (0 on invalid sizes).  The
  * workspace holds per-workgroup partial maxima of the argmax and, for an
- * in-place specdec_step, the order in which the realignment takes the rows
- * (longest moving rows first); it needs no initialisation and its contents
+ * in-place specdec_step over many long spans, the order in which the
+ * realignment takes the rows (longest moving rows first); it needs no initialisation and its contents
  * after a call are unspecified.  The size does not depend on the logit
  * dtype, so no dtype argument is taken.  One
  * workspace serves one in-flight call: calls that share a workspace must be
@@ -271,11 +271,13 @@ specdec_status_t specdec_realign_tokens(const int32_t* s_in, int64_t s_in_stride
  * One EqSpec step after the forwards (Algorithm 1, phases 2 and 3: batch
  * verification, then unpad-append-repad of the cache, the token row and the
  * attention inputs so that I1 and I2 hold for the next forward), on one
- * stream: specdec_verify_greedy, then one fused launch of the cache
- * realignment, the position ids / mask and (when s_in is not NULL) the token
- * row realignment.  In place, the verification also writes into the
- * workspace the order in which the realignment takes the rows (the longest
- * moving rows first).  Arguments as above; pm_cap must be
+ * stream: the launches of specdec_verify_greedy, then one fused launch of the
+ * cache realignment, the position ids / mask and (when s_in is not NULL) the
+ * token row realignment (in place, a few long spans take a second one).  A
+ * small step (at most 256 logit rows, a small cache) does the second launch of
+ * verification inside the realignment's.  In place over many long spans, the
+ * verification also writes into the workspace the order in which the
+ * realignment takes the rows (the longest moving rows first).  Arguments as above; pm_cap must be
  * >= W_in + k + 1.  Every output (tokens, n_acc, bonus, pad_out, w_new, the
  * workspace, pos, mask, dst, s_out, dev_status) stands apart from every
  * input (logits, draft, pad_in, src, s_in) and from the other outputs,
@@ -307,8 +309,9 @@ specdec_status_t specdec_step(const void* logits, int32_t dtype, const int32_t* 
  * of its own kernels, one kernel that clears the array's completion counts;
  * a call that fails a check enqueues nothing.
  *
- * Batches of at most 4096 logit rows (B*(k+1)) of at most 16 KB each
- * (V*4 bytes for f32, V*2 for bf16 / f16) verify in ONE launch: a workgroup
+ * Small steps take specdec_step's two launches.  Other batches of at most 4096
+ * logit rows (B*(k+1)) of at most 16 KB each (V*4 bytes for f32, V*2 for bf16 /
+ * f16) verify in ONE launch: a workgroup
  * per row, and the last row of a sequence, then the last sequence, to finish
  * merges (counted in the scratch; the realignment launch clears the counts
  * again).  The step is then two launches.  Larger batches verify in the scan
@@ -567,7 +570,8 @@ specdec_status_t specdec_varlen_rollback(const specdec_varlen_t* src, const spec
  * Kernel timers (for measurement; off by default).  specdec_timing_enable
  * takes a mask of kernels (bit 1 << SPECDEC_KERNEL_*; 0 turns the timers
  * off).  For each selected kernel the library records a pair of HIP events on
- * the launch stream around its launch (verify: around its two launches).
+ * the launch stream around its launch (verify: around its two launches; in a
+ * small step, whose second one is part of the realignment, around the first).
  * specdec_timing_query waits for the recorded events, adds their durations to
  * the totals of `kernel` (0 = verify, 1 = realign, with the fused position ids
  * / mask in specdec_step, 2 = position ids / mask alone, 3 = batch gather,

@@ -755,18 +755,19 @@ specdec_status_t step_greedy(const void* logits, int32_t dtype, const int32_t* d
   specdec::RealignLaunch rp = step_realign_launch(k, W_in, src, dst, in_place, pad_in, tokens, n_acc, pad_out, w_new, pos,
                                                   mask, pm_cap, s_in, s_in_stride, s_out, s_out_stride, pad_id, dev_status);
   hipError_t e = hipSuccess;
+  if (specdec::small_step_fits(vp, rp)) {   // faster than the one-launch verification, whose counts it leaves alone
+    e = timed(SPECDEC_KERNEL_VERIFY, st, [&] {
+      return timed(SPECDEC_KERNEL_VERIFY_SCAN, st, [&] { return specdec::launch_verify_scan(vp, st); });
+    });
+    if (e != hipSuccess) return hip_fail(e, "verify launch");
+    return step_finish(st, w_new, w_new_host, [&] { return specdec::launch_small_step(vp, rp, st); });
+  }
   if (fused_counts) {
     rp.clear_words = fused_counts;
     rp.clear_count = static_cast<uint32_t>(B) + 1u;
     e = timed(SPECDEC_KERNEL_VERIFY, st, [&] {
       return timed(SPECDEC_KERNEL_VERIFY_SCAN, st, [&] { return specdec::launch_verify_fused(vp, fused_counts, st); });
     });
-  } else if (specdec::small_step_fits(vp, rp)) {
-    e = timed(SPECDEC_KERNEL_VERIFY, st, [&] {
-      return timed(SPECDEC_KERNEL_VERIFY_SCAN, st, [&] { return specdec::launch_verify_scan(vp, st); });
-    });
-    if (e != hipSuccess) return hip_fail(e, "verify launch");
-    return step_finish(st, w_new, w_new_host, [&] { return specdec::launch_small_step(vp, rp, st); });
   } else {
     // where a walk realigns the cache in place, the merge launch also writes
     // the order it takes the rows in

@@ -771,7 +771,12 @@ specdec_status_t step_greedy(const void* logits, int32_t dtype, const int32_t* d
   } else {
     // where a walk realigns the cache in place, the merge launch also writes
     // the order it takes the rows in
-    vp.write_order = in_place && specdec::inplace_plan(src->L, B, src->H, src->D, W_in).chunks == 0;
+    if (in_place) {
+      const specdec::InplacePlan plan = specdec::inplace_plan(src->L, B, src->H, src->D, W_in, true);
+      vp.write_order = plan.chunks == 0;
+      vp.order_classes = plan.classes;
+      rp.row_group = plan.row_group;
+    }
     if (vp.write_order)
       rp.order = reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + specdec::order_offset(B, k, V));
     e = verify_launches(vp, st);

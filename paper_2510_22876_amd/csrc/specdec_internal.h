@@ -25,6 +25,7 @@ struct VerifyLaunch {
   void* workspace;           // [header][partial maxima: B*(k+1)*chunks uint64][order table]
   uint32_t* dev_status;      // may be null
   bool write_order = false;  // also write the in-place realignment order into the workspace
+  int32_t order_classes = 1; // with the moving rows in this many classes of length
 };
 
 // In-place realignment order, written by the verification merge into the
@@ -40,13 +41,16 @@ int64_t order_bytes(int64_t B);
 
 // How a cache is realigned in place: chunk by chunk (chunks > 0 workgroups a
 // span of `tpb` threads with `vec` 16-byte vectors each), or, with chunks =
-// 0, by one walk per span.
+// 0, by one walk per span, which takes the rows in the order table's order
+// (`classes` length classes, `row_group` rows at a time) where there is one.
+// `ordered`: the caller can have the table written.
 struct InplacePlan {
   int vec = 0, tpb = 0;
   int lds = 0;          // bytes of LDS a workgroup claims to bound how many share a CU
   int64_t chunks = 0;
+  int classes = 1, row_group = 32;
 };
-InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in);
+InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in, bool ordered);
 
 struct RealignLaunch {
   const void* src;
@@ -72,6 +76,7 @@ struct RealignLaunch {
   int32_t pad_id;
   // in place: the order table written by verification (NULL: the cache's order)
   const int32_t* order = nullptr;
+  int32_t row_group = 32;
   // words the launch zeroes in one extra workgroup (NULL: none)
   uint32_t* clear_words = nullptr;
   uint32_t clear_count = 0;

@@ -168,6 +168,7 @@ struct VerifyArgs {
   int64_t chunk_elems;
   int32_t chunks;               // workgroups per logit row
   int32_t* order;               // in-place realignment order table (NULL: not written)
+  int32_t order_classes;        // its length classes of moving rows
 };
 
 // Tunables of the vocabulary scan (compile-time; chosen by sweeping on
@@ -187,17 +188,6 @@ struct VerifyArgs {
 #ifndef SPECDEC_VERIFY_MAX_CHUNK
 #define SPECDEC_VERIFY_MAX_CHUNK 16384
 #endif
-// In-place realignment order that the merge writes: length classes of the
-// moving rows (longest first; 1: every moving row in the cache's order), and
-// rows per group of the walk (the walk takes the rows a group at a time, each
-// group slab by slab in the cache's order)
-#ifndef SPECDEC_INPLACE_CLASSES
-#define SPECDEC_INPLACE_CLASSES 2
-#endif
-#ifndef SPECDEC_INPLACE_ROWGROUP
-#define SPECDEC_INPLACE_ROWGROUP 32
-#endif
-
 // Scan logit elements [beg, end) of one row; 16-byte vectors over the aligned
 // interior, single elements for the unaligned head and the tail.
 template <int DT, int kTpb = kThreads, int kUnroll = SPECDEC_VERIFY_UNROLL>
@@ -282,8 +272,6 @@ __global__ __launch_bounds__(kThreads) void verify_partial_kernel(VerifyArgs a) 
 }
 
 constexpr int kFinalizeThreads = 1024;
-constexpr int kInClasses = SPECDEC_INPLACE_CLASSES;
-constexpr uint32_t kInRowGroup = SPECDEC_INPLACE_ROWGROUP;
 
 // Geometry of row i after verification: ok (pad_in in range), the new length
 // and padding; the row moves when its padding changes.
@@ -303,18 +291,18 @@ __device__ __forceinline__ RowMove row_move(const VerifyArgs& a, int i, int32_t 
 }
 
 // The in-place realignment order (one workgroup of kFinalizeThreads, after
-// the paddings): moving rows in kInClasses classes of equal length range,
+// the paddings): moving rows in order_classes classes of equal length range,
 // longest first, then the rows with nothing to move; each class in
 // increasing row order (a stable partition: per chunk of rows a ballot per
 // class, then prefixes over the waves).  The in-place walk takes the spans
 // of the longest rows first, so that the longest walks do not start last.
 __device__ void write_inplace_order(const VerifyArgs& a, int32_t w) {
   constexpr int kW = kFinalizeThreads / 64;
-  constexpr int kCls = kInClasses + 1;   // the last class: rows with nothing to move
+  constexpr int kCls = kMaxOrderClasses;
+  const int moving = a.order_classes;    // the class after them: rows with nothing to move
   __shared__ int32_t s_lo[kW], s_hi[kW];
   __shared__ int32_t s_cnt[kCls], s_start[kCls], s_carry[kCls];
   __shared__ int32_t s_wave[kCls][kW];
-  static_assert(kInClasses >= 1 && kCls <= kMaxOrderClasses, "order classes");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   int32_t lo = 0x7FFFFFFF, hi = 0;
   for (int i = tid; i < a.B; i += kFinalizeThreads) {
@@ -344,9 +332,9 @@ __device__ void write_inplace_order(const VerifyArgs& a, int32_t w) {
   }
   const int64_t range = static_cast<int64_t>(hi) - lo + 1;
   auto cls = [&](const RowMove& m) {
-    if (!m.moves) return kInClasses;
-    const int64_t c = (static_cast<int64_t>(hi) - m.len) * kInClasses / range;
-    return static_cast<int>(c < kInClasses ? c : kInClasses - 1);
+    if (!m.moves) return moving;
+    const int64_t c = (static_cast<int64_t>(hi) - m.len) * moving / range;
+    return static_cast<int>(c < moving ? c : moving - 1);
   };
   for (int i = tid; i < a.B; i += kFinalizeThreads) atomicAdd(&s_cnt[cls(row_move(a, i, w))], 1);
   __syncthreads();
@@ -626,6 +614,7 @@ struct RealignArgs {
   uint32_t clear_count;
   const int32_t* order;                  // in place: verification's order table (NULL: the cache's order)
   uint32_t span_rows;                    // spans per row: L * 2 * H
+  uint32_t row_group;                    // with the table: rows taken together, slab by slab
   uint32_t slots;                        // in place by chunks, and in a small step: spans * chunks
 };
 
@@ -863,12 +852,12 @@ __global__ __launch_bounds__(kTpb) void realign_inplace_kernel(RealignArgs a) {
   RowGeom g;
   if (a.order) {
     // the rows in the order verification wrote (longest moving rows first),
-    // kInRowGroup rows at a time, each group slab by slab in the cache's
+    // row_group rows at a time, each group slab by slab in the cache's
     // order: the index alone gives (group, slab, row, head), and one load the
     // row's geometry
     const uint32_t B = static_cast<uint32_t>(a.B), H = static_cast<uint32_t>(a.H);
     // R <= B, so a group's spans (R * span_rows <= nspans) fit 32 bits
-    const uint32_t R = kInRowGroup && kInRowGroup < B ? kInRowGroup : B;   // 0: the whole batch is one group
+    const uint32_t R = a.row_group < B ? a.row_group : B;
     const uint32_t grp_spans = R * a.span_rows;
     const uint32_t gi = lin / grp_spans;
     const uint32_t rem = lin - gi * grp_spans;
@@ -1324,6 +1313,7 @@ static VerifyArgs verify_args(const VerifyLaunch& p) {
   a.chunks = static_cast<int32_t>((p.V + a.chunk_elems - 1) / a.chunk_elems);
   a.order = p.write_order ? reinterpret_cast<int32_t*>(static_cast<char*>(p.workspace) + order_offset(p.B, p.k, p.V))
                           : nullptr;
+  a.order_classes = p.order_classes;
   return a;
 }
 
@@ -1397,22 +1387,26 @@ static void fill_token_args(RealignArgs& a, const RealignLaunch& p, int tpb) {
 }
 
 // The in-place plan, by the longest span a row can have and the number of
-// spans (the host does not know the rows' lengths).  Whole steps in us, one
-// box, walk / chunks of 64 KB / of 128 KB, the latter two with at most two
-// workgroups per CU (through LDS they do not use: more in flight spreads the
-// DRAM traffic and costs up to 15%), unless noted:
-//   spans of one chunk: to 22 KB 237 / 77 (no limit to two); to 60 KB, ragged
-//     580 / 138 (no limit), even ones 288 / 243; 5..124 KB, ragged 511 / 320 /
-//     272, even ones of 77..124 KB 416 / - / 433
-//   128 spans to 2 MB 74 / 52 / 61; 256 to 2 MB 113 / 104 / 111; 1536 of 0.45 MB
-//     101 / 93 / 97; 2048 to 0.9 MB 203 / 194 / 167; 4096 to 1 MB, ragged 365 /
-//     322 / 277, even 774 / 776 / 791; 8192 to 1 MB, ragged 620 / 582 / 498, even
-//     1336 / 1390 / 1383
-//   16384 to 0.9 MB, ragged 811 / 957 / 855; 14336 to 2 MB 2366 / 2785 / 2402
-// The walk's last round is long where few spans are long and the rest short;
-// the chunks pay the strips' bytes and launch.  The line lies where ragged
-// batches, the common ones, stop gaining; even ones lose 1 to 4% below it.
-InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in) {
+// spans (the host does not know the rows' lengths).  Whole steps in us, one box
+// a line; walk 32 / 1: the walk with the order table, 32 rows at a time in 2
+// length classes / a row at a time in 7, so that the long rows of all layers
+// come first; chunks: of 64 KB up to 1536 spans, else of 128 KB, at most two
+// workgroups a CU (through LDS they do not use: more in flight spreads the
+// DRAM traffic and costs up to 15%) unless noted.
+//   spans of one chunk: to 22 KB, walk 32 237, chunks 77 (no limit to two); to
+//     60 KB, ragged 580 / 138 (no limit), even 288 / 243; 5..124 KB, ragged 511 /
+//     272, even ones of 77..124 KB 416 / 433
+//   longer, walk 32 / walk 1 / chunks: 128 spans to 2 MB 72 / 73 / 52; 256 to 2 MB
+//     114 / 112 / 105; 512 to 2 MB 208 / 191 / 190; 1024 to 2 MB 348 / 298 / 317;
+//     2048 to 0.9 MB 194 / 131 / 168 and 294 / 177 / 184, of 128..230 KB 109 / 113 /
+//     116; 4096 to 1 MB, ragged 356 / 266 / 278, even 772 / 767 / 794; 8192 to 1
+//     MB, ragged 593 / 478 / 500, even 1354 / 1350 / 1405; 16384 to 0.9 MB 790 /
+//     819 / 855
+// 32 rows at a time, the last layers' long rows start last; one row at a time,
+// neighbouring workgroups move distant spans, which costs where there are
+// enough spans to hide the last round.  Without a table (`ordered` false: a
+// realignment alone, a sampled step) chunks take the place of walk 1.
+InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in, bool ordered) {
   InplacePlan plan;
   const int64_t longest = W_in * (D / 8);   // a row holds at most W_in columns
   const int64_t nspans = L * 2 * B * H;
@@ -1422,12 +1416,17 @@ InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_i
     plan.chunks = 1;
     return plan;
   }
-  if (longest > 32 * 256 && nspans > 8192) return plan;   // the walk
+  if (longest > 32 * 256 && nspans > (ordered ? 512 : 8192)) {   // the walk
+    plan.classes = nspans > 8192 ? 2 : kMaxOrderClasses - 1;
+    plan.row_group = nspans > 8192 ? 32 : 1;
+    return plan;
+  }
+  InplacePlan walk = plan;
   plan.vec = longest > 32 * 256 && nspans <= 1536 ? 16 : 32;
   plan.tpb = 256;
   plan.chunks = (longest + plan.vec * plan.tpb - 1) / (plan.vec * plan.tpb);
   plan.lds = 64 * 1024;
-  return nspans * plan.chunks <= 0x7FFFFFFF ? plan : InplacePlan{};
+  return nspans * plan.chunks <= 0x7FFFFFFF ? plan : walk;
 }
 
 template <int kVec, int kTpb, bool kMany>
@@ -1457,9 +1456,10 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
   a.pad_out = p.pad_out;
   a.pm_cap = p.pm_cap;
   a.order = p.in_place ? p.order : nullptr;
+  a.row_group = static_cast<uint32_t>(p.row_group);
   a.span_rows = static_cast<uint32_t>(static_cast<int64_t>(p.L) * 2 * p.H);
   const InplacePlan plan =
-      p.in_place ? inplace_plan(p.L, p.B, p.H, p.D, p.W_in) : InplacePlan{};
+      p.in_place ? inplace_plan(p.L, p.B, p.H, p.D, p.W_in, p.order != nullptr) : InplacePlan{};
   const bool by_chunk = plan.chunks > 0;
   const int tpb = by_chunk ? plan.tpb : (p.in_place ? kInTpb : kOopTpb);
   int64_t pm_blocks = 0;

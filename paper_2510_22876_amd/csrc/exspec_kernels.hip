@@ -300,7 +300,7 @@ hipError_t launch_gather(const GatherLaunch& p, hipStream_t stream) {
   const int64_t extra = pm_blocks + tok_blocks;
   const int64_t nspans = p.Lb > 0 ? static_cast<int64_t>(p.L) * 2 * p.B * p.H : 0;
   const int64_t row_vecs = static_cast<int64_t>(p.Lb) * a.vpc;
-  const int split = split_distance(nspans, row_vecs, true);
+  const int split = split_distance(row_vecs, true);
   a.misaligned = !split_spans_aligned(kPieces, split, p.batch, a.batch_span_vecs);
   const int64_t chunks = split_blocks(kPieces, kTpb, split, row_vecs, a.misaligned != 0);
   a.chunks = static_cast<uint32_t>(chunks > 0 ? chunks : 1);
@@ -354,7 +354,7 @@ hipError_t launch_writeback(const WritebackLaunch& p, hipStream_t stream) {
   const int64_t extra = p.B;
   int64_t chunks = 1;
   const int64_t row_vecs = (static_cast<int64_t>(p.Lb) + p.k + 1) * a.vpc;
-  const int split = split_distance(nspans, row_vecs, false);
+  const int split = split_distance(row_vecs, false);
   a.misaligned = !p.append_only && !split_spans_aligned(kPieces, split, p.pool, a.pool_span_vecs);
   if (!p.append_only) chunks = split_blocks(kPieces, kTpb, split, row_vecs, a.misaligned != 0);
   a.chunks = static_cast<uint32_t>(chunks);

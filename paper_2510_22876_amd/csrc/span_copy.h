@@ -121,21 +121,23 @@ inline int64_t split_blocks(int64_t vecs, bool misaligned = false) {
   return split_blocks(kPieces, kTpb, kSplit, vecs, misaligned);
 }
 
-// Distance in vectors between the two pieces of a workgroup, for `spans`
-// output spans of at most `vecs` vectors each; `padded`: every span is
-// written to that length.  Measured, whole calls in us at 64 / 512 / 1024:
-//   8192 spans of 17 KB 51.1 / 58.5 / 80.8 (147 MB), 2048 of 34 KB 30.5 / 33.6 /
-//     33.1 (70 MB), 4096 of 63 KB 78.7 / 76.5 / - (262 MB): small caches, where
-//     the workgroups that a coarse group rounds up to cost more than the
-//     memory's access pattern;
-//   16384 spans of 60 KB 340 / 306 / 299, 67584 of 59 KB 798 / 745 / 877, 16384
-//     of 120 KB 623 / 590 / 587: 512;
-//   16384 spans of 0.9 MB 3492 / 2819 / 2786, 2048 of 0.9 MB 381 / 367 / 362, but
-//     16384 of 260 KB 1185 / 1128 / 1132: 1024 for long padded spans.  Where rows
-//     end as they come (a write-back of 16 rows of 64..4096 columns) it leaves
-//     more workgroups empty: 989 / 1016 at 512 / 1024.
-inline int split_distance(int64_t spans, int64_t vecs, bool padded) {
-  if (spans * vecs * 16 <= (192ll << 20)) return 64;
+// Distance in vectors between the two pieces of a workgroup, for output spans
+// of at most `vecs` vectors each; `padded`: every span is written to that
+// length.  About 3.6 workgroups start a nanosecond, so where 512 rounds a span
+// up to more than one per 56 vectors (read and written at 6.5 TB/s), their
+// dispatch takes longer than the memory does, and 64, which rounds up to whole
+// workgroups only, is the better one.  Measured, whole calls in us at 64 / 512 /
+// 1024 (workgroups a span at 512):
+//   8192 spans of 1120 vectors (24) 51.1 / 58.5 / 80.8, write-back 48 / 67 / -;
+//   14080 of 1408 (24) 100.8 / 96.5 / 134, 3072 of 1600 (24) 33.2 / 32.2 / -, 2048 of
+//     2192 (32) 19.7 / 18.6 / -, 67584 of 3792 (40) 798 / 745 / 877, 16384 of 7776
+//     (64) 623 / 590 / 587;
+//   16384 spans of 55472 3492 / 2819 / 2786, 2048 of them 381 / 367 / 362, but 16384
+//     of 16384 1185 / 1128 / 1132: 1024 for long padded spans.  Where rows end as
+//     they come (a write-back of 16 rows of 64..4096 columns) it leaves more
+//     workgroups empty: 989 / 1016 at 512 / 1024.
+inline int split_distance(int64_t vecs, bool padded) {
+  if (vecs < 56 * split_blocks(2, 64, 512, vecs, true)) return 64;
   return padded && vecs >= 32 * 1024 ? 1024 : 512;
 }
 

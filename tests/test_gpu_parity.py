@@ -331,11 +331,13 @@ def test_inplace_chunks_split_over_launches(monkeypatch):
         _full_check(run_gpu(INPLACE_CASES[name], seed=2, variant="inplace", tokens="inplace"))
 
 
-# Out of place, the pieces of a workgroup lie 64, 512 or 1024 vectors apart by
-# the cache's and the spans' size (192 MB; 32768 vectors), with spans that start
-# on and off the boundaries of their groups and end at their edges.
+# Out of place, the pieces of a workgroup lie 64, 512 or 1024 vectors apart by the
+# spans' length (1344 and 1792 are where 24 and 32 workgroups a span become too
+# many; 32768), with spans that start on and off the boundaries of their groups
+# and end at their edges.
 OOP_CASES = {
     "split64": _inplace_case(129, [123, 122, 1, 63, 64], D=8, H=3),
+    "split64_1343": _inplace_case(1343, [1337, 1000, 64], D=8, H=3), "split512_1344": _inplace_case(1344, [1338, 1, 900], D=8, H=3),
     "split64_d24": _inplace_case(50, [44, 40, 3], D=24, H=5),
     "split512": _inplace_case(640, [634, 600, 10, 513], D=128, H=300, L=1),
     "split1024": _inplace_case(32780, [32774, 32000, 50, 8192], D=8, H=50, L=2),

@@ -558,8 +558,11 @@ typedef struct specdec_varlen {
  *               pos_cap >= src->T_cap.
  * A sequence shorter than k + 1 rows or longer than max_len, outside the
  * buffer, or with n_acc outside [0, k] keeps no row and is flagged
- * (SPECDEC_DEV_BAD_WIDTH / _BAD_ACCEPT).  cu_out, pos and dst must not overlap
- * each other or cu_in, n_acc and src: SPECDEC_ERR_INVALID_ARGUMENT.
+ * (SPECDEC_DEV_BAD_WIDTH / _BAD_ACCEPT).  Where a cu_in that falls makes
+ * sequences overlap, the kept rows stop at min(T_cap of src, B * max_len) and
+ * the sequences cut there are flagged SPECDEC_DEV_BAD_WIDTH.  cu_out, pos and
+ * dst must not overlap each other or cu_in, n_acc and src:
+ * SPECDEC_ERR_INVALID_ARGUMENT.
  */
 specdec_status_t specdec_varlen_rollback(const specdec_varlen_t* src, const specdec_varlen_t* dst,
                                          const int32_t* cu_in, const int32_t* n_acc, int32_t B,

@@ -114,16 +114,20 @@ struct VarlenArgs {
   int64_t* pos;
   int32_t B, k, max_len;
   uint32_t* dev_status;
-  int64_t rows_cap;       // rows that the kept sequences can have in all
+  int64_t rows_cap;       // rows that the kept sequences can have in all (below 2^31)
   uint32_t chunks;        // workgroups per (layer, K/V) slab
   uint32_t block_base;    // compaction workgroups of earlier launches
   uint32_t pos_blocks;    // position-id workgroups (first launch only)
 };
 
 // Kept lengths and their running sum (one workgroup, B in stripes of 1024).
+// Sequences of a nondecreasing cu_in are disjoint, so their rows fit rows_cap.
+// Offsets that fall make sequences overlap; the sum (saturating, it can pass
+// 2^32) then stops at rows_cap, so that the offsets never fall and every output row
+// below cu_out[B] lies in the sequence that a search in them finds.
 __global__ __launch_bounds__(kOneBlock) void varlen_offsets_kernel(VarlenArgs a) {
-  __shared__ int32_t wsum[kOneBlock / 64];
-  __shared__ int32_t carry;
+  __shared__ uint32_t wsum[kOneBlock / 64];
+  __shared__ uint32_t carry;
   if (threadIdx.x == 0) {
     carry = 0;
     a.cu_out[0] = 0;
@@ -146,20 +150,25 @@ __global__ __launch_bounds__(kOneBlock) void varlen_offsets_kernel(VarlenArgs a)
       }
     }
     // inclusive scan of keep over the stripe
-    int32_t v = keep;
+    uint32_t v = static_cast<uint32_t>(keep);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-      const int32_t o = __shfl_up(v, off);
-      if (lane >= off) v += o;
+      const uint32_t o = __shfl_up(v, off);
+      if (lane >= off) v = __builtin_elementwise_add_sat(v, o);
     }
     if (lane == 63) wsum[wave] = v;
     __syncthreads();
-    int32_t before = carry;
+    uint32_t end = carry;
 #pragma unroll
-    for (int q = 0; q < kOneBlock / 64; ++q) before += q < wave ? wsum[q] : 0;
-    if (i < a.B) a.cu_out[i + 1] = before + v;
+    for (int q = 0; q < kOneBlock / 64; ++q) end = __builtin_elementwise_add_sat(end, q < wave ? wsum[q] : 0u);
+    end = __builtin_elementwise_add_sat(end, v);
+    if (i < a.B) {
+      const uint32_t most = static_cast<uint32_t>(a.rows_cap);
+      a.cu_out[i + 1] = static_cast<int32_t>(end < most ? end : most);
+      if (keep > 0 && end > most && a.dev_status) atomicOr(a.dev_status, kBadWidth);
+    }
     __syncthreads();
-    if (threadIdx.x == kOneBlock - 1) carry = before + v;
+    if (threadIdx.x == kOneBlock - 1) carry = end;
     __syncthreads();
   }
 }
@@ -200,9 +209,7 @@ __global__ __launch_bounds__(kTpb) void varlen_compact_kernel(VarlenArgs a) {
   auto row_of = [&](int64_t u) {
     return static_cast<int32_t>(a.row_shift >= 0 ? u >> a.row_shift : u / a.row_vecs);
   };
-  // rows in all; offsets that do not come from disjoint sequences stop at the buffer
-  int64_t rows = cu_scalar(a.B);
-  if (rows > a.rows_cap) rows = a.rows_cap;
+  const int64_t rows = cu_scalar(a.B);   // in all, at most rows_cap
   if (b < a.pos_blocks) {
     // position ids of the kept rows: 4*kTpb rows per workgroup
     const int64_t r0 = static_cast<int64_t>(b) * (4 * kTpb);
@@ -285,10 +292,11 @@ hipError_t launch_varlen_rollback(const VarlenLaunch& p, hipStream_t stream) {
   a.k = p.k;
   a.max_len = p.max_len;
   a.dev_status = p.dev_status;
+  a.rows_cap = static_cast<int64_t>(p.max_len) * p.B < p.src_T ? static_cast<int64_t>(p.max_len) * p.B : p.src_T;
+  if (a.rows_cap > INT32_MAX) a.rows_cap = INT32_MAX;   // cu_in names no row beyond
   hipLaunchKernelGGL(varlen_offsets_kernel, dim3(1), dim3(kOneBlock), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  a.rows_cap = static_cast<int64_t>(p.max_len) * p.B < p.src_T ? static_cast<int64_t>(p.max_len) * p.B : p.src_T;
   const int64_t pos_blocks = p.pos ? (a.rows_cap + 4 * kTpb - 1) / (4 * kTpb) : 0;
   // a slab may start anywhere: room for the extra group of the aligned tiling
   const int64_t chunks = split_blocks<kPieces, kTpb, kSplit>(a.rows_cap * a.row_vecs, true);

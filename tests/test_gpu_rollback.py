@@ -245,3 +245,24 @@ def test_varlen_rollback_short_and_skipped_sequences(sd, monkeypatch, B, k, L, H
         exp[:, :, ecu[i]: ecu[i + 1]] = src[:, :, cu[i]: cu[i] + keep[i]]
         epos[ecu[i]: ecu[i + 1]] = np.arange(keep[i])
     assert np.array_equal(got, exp) and np.array_equal(pos, epos)
+
+
+# Offsets that fall (cu_in has to be nondecreasing) make sequences overlap: the
+# output stops at the rows that the buffer can hold, flagged, with every row
+# from its sequence, also where the kept lengths pass 2^31 in all.
+@pytest.mark.parametrize("T,cu", [(40, [0, 30, 10, 40, 40]), (70000, [0, 70000] * 32768 + [0])], ids=["short", "beyond_2_31"])
+def test_varlen_rollback_falling_offsets_stop_at_the_buffer(sd, T, cu):
+    say(f"varlen falling offsets T={T} B={len(cu) - 1}")
+    B = len(cu) - 1
+    src = np.random.default_rng(T).integers(0, 0x10000, size=(1, 2, T, 1, 8), dtype=np.uint16)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    got, cu_out, pos = _run_varlen(sd, src, np.array(cu, np.int32), np.zeros(B, np.int32), 0, T, status=status)
+    assert int(status.cpu()[0]) == sd.DEV_BAD_WIDTH
+    ends, rows = [0], []
+    for b, e in zip(cu, cu[1:]):
+        take = min(max(e - b, 0), T - ends[-1])
+        ends.append(ends[-1] + take)
+        rows.append(np.arange(b, b + take))
+    rows, index = np.concatenate(rows), np.concatenate([np.arange(len(r)) for r in rows])
+    assert np.array_equal(cu_out, ends)
+    assert np.array_equal(got, src[:, :, rows]) and np.array_equal(pos, index)

@@ -654,6 +654,7 @@ specdec_status_t specdec_realign_kv(const specdec_kv_t* src, const specdec_kv_t*
   p.w_new = w_new;
   p.dev_status = dev_status;
   p.in_place = in_place;
+  if (in_place) p.plan = specdec::inplace_plan(src->L, src->B, src->H, src->D, W_in, false);
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e = timed(SPECDEC_KERNEL_REALIGN, st, [&] { return specdec::launch_realign(p, st); });
   if (e != hipSuccess) return hip_fail(e, "realign launch");
@@ -754,6 +755,7 @@ specdec_status_t step_greedy(const void* logits, int32_t dtype, const int32_t* d
                            bonus, pad_out, w_new, workspace, dev_status};
   specdec::RealignLaunch rp = step_realign_launch(k, W_in, src, dst, in_place, pad_in, tokens, n_acc, pad_out, w_new, pos,
                                                   mask, pm_cap, s_in, s_in_stride, s_out, s_out_stride, pad_id, dev_status);
+  if (in_place) rp.plan = specdec::inplace_plan(src->L, B, src->H, src->D, W_in, !fused_counts);
   hipError_t e = hipSuccess;
   if (specdec::small_step_fits(vp, rp)) {   // faster than the one-launch verification, whose counts it leaves alone
     e = timed(SPECDEC_KERNEL_VERIFY, st, [&] {
@@ -769,16 +771,12 @@ specdec_status_t step_greedy(const void* logits, int32_t dtype, const int32_t* d
       return timed(SPECDEC_KERNEL_VERIFY_SCAN, st, [&] { return specdec::launch_verify_fused(vp, fused_counts, st); });
     });
   } else {
-    // where a walk realigns the cache in place, the merge launch also writes
-    // the order it takes the rows in
-    if (in_place) {
-      const specdec::InplacePlan plan = specdec::inplace_plan(src->L, B, src->H, src->D, W_in, true);
-      vp.write_order = plan.chunks == 0;
-      vp.order_classes = plan.classes;
-      rp.row_group = plan.row_group;
-    }
-    if (vp.write_order)
+    // where the cache is realigned in the order table's order, the merge launch writes the table
+    if (in_place && rp.plan.table) {
+      vp.write_order = true;
+      vp.order_classes = rp.plan.classes;
       rp.order = reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + specdec::order_offset(B, k, V));
+    }
     e = verify_launches(vp, st);
   }
   if (e != hipSuccess) return hip_fail(e, "verify launch");
@@ -933,9 +931,10 @@ specdec_status_t specdec_step_sample(const void* logits, const void* draft_logit
                            B, k, V, W_in, tokens, n_acc, bonus, pad_out, w_new, workspace, dev_status};
   hipError_t e = sample_launches(sp, st);
   if (e != hipSuccess) return hip_fail(e, "stochastic verify launch");
-  const specdec::RealignLaunch rp =
+  specdec::RealignLaunch rp =
       step_realign_launch(k, W_in, src, dst, in_place, pad_in, tokens, n_acc, pad_out, w_new, pos, mask, pm_cap, s_in,
                           s_in_stride, s_out, s_out_stride, pad_id, dev_status);
+  if (in_place) rp.plan = specdec::inplace_plan(src->L, B, src->H, src->D, W_in, false);
   return step_finish(st, w_new, w_new_host, [&] { return specdec::launch_realign(rp, st); });
 }
 

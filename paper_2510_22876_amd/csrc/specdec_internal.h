@@ -42,12 +42,14 @@ int64_t order_bytes(int64_t B);
 // How a cache is realigned in place: chunk by chunk (chunks > 0 workgroups a
 // span of `tpb` threads with `vec` 16-byte vectors each), or, with chunks =
 // 0, by one walk per span, which takes the rows in the order table's order
-// (`classes` length classes, `row_group` rows at a time) where there is one.
-// `ordered`: the caller can have the table written.
+// (`classes` length classes, `row_group` rows at a time) where the plan says
+// that there is one.  `ordered`: the caller can have the table written; it then
+// does so, and passes its address, for a plan whose `table` is set.
 struct InplacePlan {
   int vec = 0, tpb = 0;
   int lds = 0;          // bytes of LDS a workgroup claims to bound how many share a CU
   int64_t chunks = 0;
+  bool table = false;
   int classes = 1, row_group = 32;
 };
 InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in, bool ordered);
@@ -74,9 +76,8 @@ struct RealignLaunch {
   int64_t s_in_stride, s_out_stride;
   const int32_t* tokens;
   int32_t pad_id;
-  // in place: the order table written by verification (NULL: the cache's order)
-  const int32_t* order = nullptr;
-  int32_t row_group = 32;
+  InplacePlan plan;                 // in place
+  const int32_t* order = nullptr;   // the order table written by verification, where the plan has one
   // words the launch zeroes in one extra workgroup (NULL: none)
   uint32_t* clear_words = nullptr;
   uint32_t clear_count = 0;

@@ -1419,11 +1419,13 @@ InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_i
     return plan;
   }
   if (longest > 32 * 256 && (B == 1 || nspans > (ordered ? 512 : 8192))) {   // the walk
+    plan.table = ordered;
     plan.classes = nspans > 8192 ? 2 : kMaxOrderClasses - 1;
     plan.row_group = nspans > 8192 ? 32 : 1;
     return plan;
   }
   InplacePlan walk = plan;
+  walk.table = ordered;
   plan.vec = longest > 32 * 256 && nspans <= 1536 ? 16 : 32;
   plan.tpb = 256;
   plan.chunks = (longest + plan.vec * plan.tpb - 1) / (plan.vec * plan.tpb);
@@ -1457,12 +1459,12 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
   a.mask = p.mask;
   a.pad_out = p.pad_out;
   a.pm_cap = p.pm_cap;
+  const InplacePlan& plan = p.plan;
+  if (p.in_place && plan.table != (p.order != nullptr)) return hipErrorInvalidValue;   // a table unread, or missing
   a.order = p.in_place ? p.order : nullptr;
-  a.row_group = static_cast<uint32_t>(p.row_group);
+  a.row_group = static_cast<uint32_t>(plan.row_group);
   a.span_rows = static_cast<uint32_t>(static_cast<int64_t>(p.L) * 2 * p.H);
-  const InplacePlan plan =
-      p.in_place ? inplace_plan(p.L, p.B, p.H, p.D, p.W_in, p.order != nullptr) : InplacePlan{};
-  const bool by_chunk = plan.chunks > 0;
+  const bool by_chunk = p.in_place && plan.chunks > 0;
   const int tpb = by_chunk ? plan.tpb : (p.in_place ? kInTpb : kOopTpb);
   int64_t pm_blocks = 0;
   a.pm_col_blocks = 1;

@@ -774,8 +774,10 @@ specdec_status_t step_greedy(const void* logits, int32_t dtype, const int32_t* d
     // where the cache is realigned in the order table's order, the merge launch writes the table
     if (in_place && rp.plan.table) {
       vp.write_order = true;
-      vp.order_classes = rp.plan.classes;
+      vp.order_by_row = rp.plan.by_row;
+      vp.order_even_len = rp.plan.even_len;
       rp.order = reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + specdec::order_offset(B, k, V));
+      rp.order_group = reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + specdec::kOrderGroupOffset);
     }
     e = verify_launches(vp, st);
   }

@@ -8,7 +8,8 @@
 namespace specdec {
 
 constexpr int kThreads = 256;          // every kernel: 4 wavefronts of 64
-constexpr size_t kWsHeaderBytes = 256; // reserved, keeps the partial maxima 256-byte aligned
+constexpr size_t kWsHeaderBytes = 256; // single words, keeps the partial maxima 256-byte aligned
+constexpr size_t kOrderGroupOffset = 4;  // of them: the rows the in-place walk takes at a time, beside the order table
 constexpr int64_t kMaxVerifyChunks = 64;  // workgroups per logit row in the verify scan
 
 struct VerifyLaunch {
@@ -25,7 +26,7 @@ struct VerifyLaunch {
   void* workspace;           // [header][partial maxima: B*(k+1)*chunks uint64][order table]
   uint32_t* dev_status;      // may be null
   bool write_order = false;  // also write the in-place realignment order into the workspace
-  int32_t order_classes = 1; // with the moving rows in this many classes of length
+  int32_t order_by_row = 0, order_even_len = 0;  // InplacePlan's
 };
 
 // In-place realignment order, written by the verification merge into the
@@ -42,15 +43,17 @@ int64_t order_bytes(int64_t B);
 // How a cache is realigned in place: chunk by chunk (chunks > 0 workgroups a
 // span of `tpb` threads with `vec` 16-byte vectors each), or, with chunks =
 // 0, by one walk per span, which takes the rows in the order table's order
-// (`classes` length classes, `row_group` rows at a time) where the plan says
-// that there is one.  `ordered`: the caller can have the table written; it then
-// does so, and passes its address, for a plan whose `table` is set.
+// where the plan says that there is one, or puts them in order itself.
+// `ordered`: the caller can have the table written; it then does so, and passes
+// its address, for a plan whose `table` is set.
 struct InplacePlan {
   int vec = 0, tpb = 0;
   int lds = 0;          // bytes of LDS a workgroup claims to bound how many share a CU
   int64_t chunks = 0;
   bool table = false;
-  int classes = 1, row_group = 32;
+  bool sorted = false;  // a walk whose waves put the rows in order themselves
+  int even_len = 0;     // columns from which on even lengths are so called
+  int by_row = 0;       // the rows one at a time: 0 never, 1 where their lengths are uneven, 2 always
 };
 InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in, bool ordered);
 
@@ -78,6 +81,7 @@ struct RealignLaunch {
   int32_t pad_id;
   InplacePlan plan;                 // in place
   const int32_t* order = nullptr;   // the order table written by verification, where the plan has one
+  const int32_t* order_group = nullptr;
   // words the launch zeroes in one extra workgroup (NULL: none)
   uint32_t* clear_words = nullptr;
   uint32_t clear_count = 0;

@@ -10,14 +10,16 @@
 //                      last-workgroup-done counter: a device-scope fence and
 //                      atomic per workgroup costs more than a kernel boundary.
 //   realign_oop        out-of-place unpad-append-repad of the bf16 KV cache:
-//                      one workgroup per 16 KB chunk of a (layer, K/V, row,
-//                      head) span, 128-bit loads and stores.
-//   realign_inplace    in-place variant for many long spans: one workgroup
-//                      walks a whole span in the direction of its shift, a
-//                      barrier between the reads and the writes of each chunk.
+//                      64-thread workgroups, two 1 KB pieces of a (layer,
+//                      K/V, row, head) span each, 128-bit loads and stores.
+//   realign_inplace    in-place variant for long spans: one workgroup walks a
+//                      whole span in the direction of its shift, a barrier
+//                      between the reads and the writes of each chunk.
 //   realign_chunk,     in-place variant for short spans and for few long ones:
 //   realign_strips     a workgroup per chunk of a span, all at once, then the
 //                      few vectors that cross from a chunk to the next.
+//   small_step         a small step's merge of the scan and its realignment, in
+//                      one launch.
 //   posmask blocks     position ids / mask of invariant I2, appended to either
 //                      realign grid (or launched alone).
 //
@@ -168,7 +170,9 @@ struct VerifyArgs {
   int64_t chunk_elems;
   int32_t chunks;               // workgroups per logit row
   int32_t* order;               // in-place realignment order table (NULL: not written)
-  int32_t order_classes;        // its length classes of moving rows
+  int32_t* order_group;         // the rows that the walk takes at a time
+  int32_t order_even_len;
+  int32_t order_by_row;         // 2: rows one at a time; 1: where their lengths are uneven; 0: never
 };
 
 // Tunables of the vocabulary scan (compile-time; chosen by sweeping on
@@ -291,32 +295,36 @@ __device__ __forceinline__ RowMove row_move(const VerifyArgs& a, int i, int32_t 
 }
 
 // The in-place realignment order (one workgroup of kFinalizeThreads, after
-// the paddings): moving rows in order_classes classes of equal length range,
-// longest first, then the rows with nothing to move; each class in
-// increasing row order (a stable partition: per chunk of rows a ballot per
-// class, then prefixes over the waves).  The in-place walk takes the spans
-// of the longest rows first, so that the longest walks do not start last.
+// the paddings): moving rows in classes of equal length range, longest first,
+// then the rows with nothing to move; each class in increasing row order (a
+// stable partition: per chunk of rows a ballot per class, then prefixes over
+// the waves).  The in-place walk takes the spans of the longest rows first, so
+// that the longest walks do not start last.  It takes them one at a time (in
+// 7 classes) or, for a cache of many spans or even lengths, 32 (in 2): see
+// inplace_plan.
 __device__ void write_inplace_order(const VerifyArgs& a, int32_t w) {
   constexpr int kW = kFinalizeThreads / 64;
   constexpr int kCls = kMaxOrderClasses;
-  const int moving = a.order_classes;    // the class after them: rows with nothing to move
-  __shared__ int32_t s_lo[kW], s_hi[kW];
+  __shared__ int32_t s_lo[kW], s_hi[kW], s_movers[kW];
   __shared__ int32_t s_cnt[kCls], s_start[kCls], s_carry[kCls];
   __shared__ int32_t s_wave[kCls][kW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  int32_t lo = 0x7FFFFFFF, hi = 0;
+  int32_t lo = 0x7FFFFFFF, hi = 0, movers = 0;
   for (int i = tid; i < a.B; i += kFinalizeThreads) {
     const RowMove m = row_move(a, i, w);
     if (m.moves) {
       lo = m.len < lo ? m.len : lo;
       hi = m.len > hi ? m.len : hi;
+      movers = 1;
     }
   }
+  movers = __popcll(__ballot(movers != 0));   // of this wave, at least
   hi = wave_max_i32(hi);
   lo = -wave_max_i32(-lo);
   if (lane == 0) {
     s_hi[wv] = hi;
     s_lo[wv] = lo;
+    s_movers[wv] = movers;
   }
   if (tid < kCls) {
     s_cnt[tid] = 0;
@@ -325,12 +333,19 @@ __device__ void write_inplace_order(const VerifyArgs& a, int32_t w) {
   __syncthreads();
   hi = s_hi[0];
   lo = s_lo[0];
+  movers = s_movers[0];
 #pragma unroll
   for (int q = 1; q < kW; ++q) {
+    movers += s_movers[q];
     hi = s_hi[q] > hi ? s_hi[q] : hi;
     lo = s_lo[q] < lo ? s_lo[q] : lo;
   }
   const int64_t range = static_cast<int64_t>(hi) - lo + 1;
+  // even: at least five rows, of lengths within a quarter of the longest
+  const bool by_row = a.order_by_row == 2 ||
+                      (a.order_by_row == 1 && (movers < 5 || lo < hi - hi / 4 || hi < a.order_even_len));
+  const int moving = by_row ? kCls - 1 : 2;    // the class after them: rows with nothing to move
+  if (tid == 0) *a.order_group = by_row ? 1 : 32;
   auto cls = [&](const RowMove& m) {
     if (!m.moves) return moving;
     const int64_t c = (static_cast<int64_t>(hi) - m.len) * moving / range;
@@ -571,6 +586,7 @@ __global__ __launch_bounds__(kFusedThreads) void verify_fused_kernel(FusedVerify
 constexpr int kOopVec = SPECDEC_OOP_VEC, kOopTpb = SPECDEC_OOP_TPB, kOopNt = SPECDEC_OOP_NT;
 constexpr int kInVec = SPECDEC_INPLACE_VEC, kInTpb = SPECDEC_INPLACE_TPB, kInNt = SPECDEC_INPLACE_NT;
 static_assert(kOopTpb % 64 == 0 && kInTpb % 64 == 0, "workgroups are whole wavefronts");
+constexpr int kCus = 256;        // compute units of the GPU
 constexpr int kSmallTpb = 256;   // threads of a small step's merged launch
 // A small step: workgroups that move the cache, and bytes that they merge in
 // all (out of place, in place).  Steps in us, three launches / two: 1024
@@ -613,8 +629,10 @@ struct RealignArgs {
   uint32_t* clear_words;                 // one more workgroup zeroes these (NULL: none)
   uint32_t clear_count;
   const int32_t* order;                  // in place: verification's order table (NULL: the cache's order)
+  const int32_t* order_group;            // with the table, and row_group 0: rows taken together
   uint32_t span_rows;                    // spans per row: L * 2 * H
-  uint32_t row_group;                    // with the table: rows taken together, slab by slab
+  uint32_t row_group;                    // ordered rows taken together, slab by slab (0: as order_group says)
+  int32_t len_half, len_quarter;         // longest rows whose spans fit half / a quarter of a walk's chunk
   uint32_t slots;                        // in place by chunks, and in a small step: spans * chunks
 };
 
@@ -789,13 +807,14 @@ __device__ __forceinline__ void hold(const u32x4& v) {
   asm volatile("" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));
 }
 
-// Loads chunk [lo, lo + kTpb*kVec) (clipped to [0, n); indices outside are
-// clamped, their values unused) of one row's kept vectors, which start at
+// Loads the part that wave `wave` of those on the span has of the chunk from
+// `lo` on, 64*kVec vectors each (clipped to [0, n); indices outside are
+// clamped, their values unused), of one row's kept vectors, which start at
 // `from` within the span.  A wave that is outside as a whole loads nothing
 // (ragged rows of 5..124 KB: 511 us a step with its loads, 425 without).
-template <int kVec, int kTpb, int kNt>
-__device__ __forceinline__ void load_chunk(const u32x4* base, int64_t from, int64_t lo, int64_t n, u32x4 (&v)[kVec]) {
-  const int64_t w0 = lo + static_cast<int64_t>(wave_index()) * (64 * kVec);   // the wave's first vector
+template <int kVec, int kNt>
+__device__ __forceinline__ void load_chunk(const u32x4* base, int64_t from, int64_t lo, int64_t n, int wave, u32x4 (&v)[kVec]) {
+  const int64_t w0 = lo + static_cast<int64_t>(wave) * (64 * kVec);   // the wave's first vector
   if (w0 >= n || w0 + 64 * kVec <= 0) return;   // the whole wave is outside
   const int64_t t0 = w0 + (threadIdx.x & 63);
 #pragma unroll
@@ -806,9 +825,9 @@ __device__ __forceinline__ void load_chunk(const u32x4* base, int64_t from, int6
   }
 }
 
-template <int kVec, int kTpb, int kNt>
-__device__ __forceinline__ void store_chunk(u32x4* base, int64_t to, int64_t lo, int64_t n, const u32x4 (&v)[kVec]) {
-  const int64_t w0 = lo + static_cast<int64_t>(wave_index()) * (64 * kVec);   // the wave's first vector
+template <int kVec, int kNt>
+__device__ __forceinline__ void store_chunk(u32x4* base, int64_t to, int64_t lo, int64_t n, int wave, const u32x4 (&v)[kVec]) {
+  const int64_t w0 = lo + static_cast<int64_t>(wave) * (64 * kVec);   // the wave's first vector
   const int lane = static_cast<int>(threadIdx.x & 63);
   u32x4* wb = base + (to + w0);
 #pragma unroll
@@ -824,6 +843,114 @@ __device__ __forceinline__ void store_chunk(u32x4* base, int64_t to, int64_t lo,
 // stay in flight across it.
 __device__ __forceinline__ void exec_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
+// The moving rows of a batch of at most 64, put in order by each wave for
+// itself, one lane a row, where verification writes no order table (a
+// realignment alone).  Rows of unequal lengths go longest first, all spans of
+// one row and then the next row's, so that no long walk starts last; where half
+// of them reach half of the longest and the spans are many, slab by slab, as
+// neighbouring workgroups on neighbouring spans matter more then.  Rows within
+// a quarter of the longest keep the cache's order, row_group at a time.  Spans
+// of uneven rows that fit half or a quarter of a chunk go two or four to a
+// workgroup (6144 spans of 5 to 232 KB 155 -> 137 us).  What a workgroup spends
+// here counts: it has the CU to itself, and with the longest, the shortest and
+// the sum of the lengths kept along in the loop those took 152.
+struct OrderedRows {
+  RowGeom row;      // lane i: row i
+  bool moves;
+  int rank;         // its place among the rows that move
+  int count;        // of them
+  bool even;
+  bool together;    // uneven: slab by slab
+  // `flag`: this wave reports the rows that it finds out of range
+  __device__ __forceinline__ OrderedRows(const RealignArgs& a, bool flag) {
+    const int lane = static_cast<int>(threadIdx.x & 63);
+    const int32_t w = load_invariant(a.w_new);
+    uint32_t err = 0u;
+    moves = false;
+    row = RowGeom{0, 0, 0, 0};
+    if (lane < a.B) {
+      err = geometry_of(a, w, a.pad_in[lane], a.n_acc[lane], row);
+      moves = err == 0u && row.pad_out != row.pad_in;
+    }
+    if (flag && err && a.dev_status) atomicOr(a.dev_status, err);
+    const unsigned long long movers = __ballot(moves);
+    count = __popcll(movers);
+    // one key a row: its length (at most 2^24), then its index; 0 for a row that stays
+    const uint32_t key = moves ? static_cast<uint32_t>(row.len) << 6 | static_cast<uint32_t>(63 - lane) : 0u;
+    rank = 0;
+    for (int j = 0; j < a.B; j += 8)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) rank += __builtin_amdgcn_readlane(key, j + u) > key ? 1 : 0;
+    even = together = false;
+    if (count == 0 || a.row_group == 1u) return;
+    auto length_at = [&](int r) { return __builtin_amdgcn_readlane(key, __builtin_ctzll(__ballot(moves && rank == r))) >> 6; };
+    const uint32_t longest = length_at(0);
+    even = length_at(count - 1) >= longest - longest / 4;
+    together = a.nspans > 2048u && 2u * length_at(count / 2) >= longest;
+    if (even) rank = __popcll(movers & ((1ull << lane) - 1ull));
+  }
+  // The lin-th workgroup has the spans j .. j + share - 1 (in the cache's
+  // order) of row row_u with geometry g; false past the last.
+  __device__ __forceinline__ bool find(const RealignArgs& a, uint32_t lin, uint32_t& j, uint32_t& share, uint32_t& row_u,
+                                       RowGeom& g) const {
+    const uint32_t S = a.span_rows;
+    uint32_t n = static_cast<uint32_t>(count), r;
+    share = 1u;
+    if (even) {
+      if (lin >= n * S) return false;
+      const uint32_t H = static_cast<uint32_t>(a.H), R = a.row_group < n ? a.row_group : n;
+      const uint32_t gi = lin / (R * S);
+      const uint32_t rem = lin - gi * (R * S);
+      const uint32_t rows_here = n - gi * R < R ? n - gi * R : R;
+      const uint32_t slab = rem / (rows_here * H);
+      const uint32_t rr = rem - slab * rows_here * H;
+      r = rr / H;
+      j = slab * H + (rr - r * H);
+      r += gi * R;
+    } else {
+      uint32_t first = 0u, units = S;   // of the rows with this share: the first one's rank, workgroups a row
+      n = __popcll(__ballot(moves && row.len > a.len_half));
+      if (lin >= n * units) {
+        lin -= n * units;
+        first = n;
+        share = 2u;
+        units = (S + 1u) / 2u;
+        n = __popcll(__ballot(moves && row.len > a.len_quarter)) - first;
+        if (lin >= n * units) {
+          lin -= n * units;
+          first += n;
+          share = 4u;
+          units = (S + 3u) / 4u;
+          n = static_cast<uint32_t>(count) - first;
+          if (lin >= n * units) return false;
+        }
+      }
+      // together: slab by slab where a slab's heads share out evenly
+      const uint32_t H = static_cast<uint32_t>(a.H);
+      uint32_t u;
+      if (together) {
+        const uint32_t hu = H % share == 0u ? H / share : 1u;
+        const uint32_t block = lin / (n * hu);
+        const uint32_t rem = lin - block * (n * hu);
+        r = rem / hu;
+        u = block * hu + (rem - r * hu);
+      } else {
+        r = lin / units;
+        u = lin - r * units;
+      }
+      r += first;
+      j = u * share;
+    }
+    const int i = __builtin_ctzll(__ballot(moves && rank == static_cast<int>(r)));
+    row_u = static_cast<uint32_t>(i);
+    g.pad_in = __builtin_amdgcn_readlane(row.pad_in, i);
+    g.pad_out = __builtin_amdgcn_readlane(row.pad_out, i);
+    g.len = __builtin_amdgcn_readlane(row.len, i);
+    g.w = __builtin_amdgcn_readlane(row.w, i);
+    return true;
+  }
+};
+
 // In place: one workgroup per span moves the row's kept vectors [from, from+n)
 // to [to, to+n) in chunks of kTpb*kVec, walking from the top for a shift to
 // higher addresses and from the bottom for a shift to lower ones.  The next
@@ -831,7 +958,9 @@ __device__ __forceinline__ void exec_barrier() { asm volatile("s_barrier" ::: "m
 // are issued before the current chunk is stored; a barrier after the current
 // chunk's loads have landed keeps every read of a chunk ahead of every write
 // to it.
-template <int kVec, int kTpb, int kNt>
+// With kSorted the rows are ordered here (OrderedRows), and short ones have two
+// or four spans on a workgroup, so many waves each.
+template <int kVec, int kTpb, int kNt, bool kSorted>
 __global__ __launch_bounds__(kTpb) void realign_inplace_kernel(RealignArgs a) {
   if (blockIdx.x < a.extra_blocks) {
     extra_block<kTpb>(a, blockIdx.x);
@@ -848,28 +977,53 @@ __global__ __launch_bounds__(kTpb) void realign_inplace_kernel(RealignArgs a) {
   const uint32_t grp = rel >> 3;
   const uint32_t lin =
       static_cast<uint64_t>(grp) * 8u + 8u <= a.nspans ? (grp << 3) + ((rel + grp) & 7u) : rel;
+  constexpr int kWavesHere = kTpb / 64;
+  static_assert(kWavesHere == 4, "four waves share out");
   uint32_t span;
   RowGeom g;
-  if (a.order) {
+  int waves = kWavesHere, wave = wave_index();   // on the span, and this one's place among them
+  bool idle = false;                             // a wave without a span
+  if constexpr (kSorted) {
+    const OrderedRows rows(a, rel == 0u && threadIdx.x < 64);
+    uint32_t j, share, row_u;
+    if (!rows.find(a, lin, j, share, row_u, g)) return;
+    waves = kWavesHere / static_cast<int>(share);
+    j += static_cast<uint32_t>(wave_index() / waves);
+    wave = wave_index() % waves;
+    idle = j >= a.span_rows;
+    const uint32_t slab = j / static_cast<uint32_t>(a.H);
+    span = (slab * static_cast<uint32_t>(a.B) + row_u) * static_cast<uint32_t>(a.H) + (j - slab * static_cast<uint32_t>(a.H));
+  } else if (a.order) {
     // the rows in the order verification wrote (longest moving rows first),
     // row_group rows at a time, each group slab by slab in the cache's
     // order: the index alone gives (group, slab, row, head), and one load the
-    // row's geometry
+    // row's geometry.  Where verification chose the group, the entry for rows
+    // one at a time is loaded along with the choice.
     const uint32_t B = static_cast<uint32_t>(a.B), H = static_cast<uint32_t>(a.H);
-    // R <= B, so a group's spans (R * span_rows <= nspans) fit 32 bits
-    const uint32_t R = a.row_group < B ? a.row_group : B;
-    const uint32_t grp_spans = R * a.span_rows;
-    const uint32_t gi = lin / grp_spans;
-    const uint32_t rem = lin - gi * grp_spans;
-    const uint32_t rows_here = B - gi * R < R ? B - gi * R : R;
-    const uint32_t slab = rem / (rows_here * H);
-    const uint32_t rr = rem - slab * rows_here * H;
-    const uint32_t r = rr / H, h = rr - r * H;
-    const int32_t* info = a.order + 4 * static_cast<int64_t>(gi * R + r);
-    const uint32_t row_u = static_cast<uint32_t>(load_invariant(info));
-    g.pad_in = load_invariant(info + 1);
-    g.pad_out = load_invariant(info + 2);
-    g.len = load_invariant(info + 3);
+    const uint32_t group = a.row_group ? a.row_group : static_cast<uint32_t>(load_invariant(a.order_group));
+    uint32_t at = lin / a.span_rows, row_u = 0u;
+    uint32_t slab = (lin - at * a.span_rows) / H, h = (lin - at * a.span_rows) - slab * H;
+    auto entry = [&] {
+      const int32_t* info = a.order + 4 * static_cast<int64_t>(at);
+      row_u = static_cast<uint32_t>(load_invariant(info));
+      g.pad_in = load_invariant(info + 1);
+      g.pad_out = load_invariant(info + 2);
+      g.len = load_invariant(info + 3);
+    };
+    if (a.row_group <= 1u) entry();
+    if (group > 1u) {
+      // R <= B, so a group's spans (R * span_rows <= nspans) fit 32 bits
+      const uint32_t R = group < B ? group : B;
+      const uint32_t grp_spans = R * a.span_rows;
+      const uint32_t gi = lin / grp_spans;
+      const uint32_t rem = lin - gi * grp_spans;
+      const uint32_t rows_here = B - gi * R < R ? B - gi * R : R;
+      slab = rem / (rows_here * H);
+      const uint32_t rr = rem - slab * rows_here * H;
+      at = gi * R + rr / H;
+      h = rr - (rr / H) * H;
+      entry();
+    }
     span = (slab * B + row_u) * H + h;
   } else {
     span = lin;
@@ -885,33 +1039,33 @@ __global__ __launch_bounds__(kTpb) void realign_inplace_kernel(RealignArgs a) {
   if (s == 0) return;  // no shift: the row is already in place (uniform acceptance)
   const int64_t vpc = a.vpc;
   u32x4* base = a.dst + static_cast<int64_t>(span) * a.dst_span_vecs;
-  const int64_t n = static_cast<int64_t>(g.len) * vpc;
+  const int64_t n = idle ? 0 : static_cast<int64_t>(g.len) * vpc;
   const int64_t from = static_cast<int64_t>(g.pad_in) * vpc;
   const int64_t to = static_cast<int64_t>(g.pad_out) * vpc;
-  constexpr int64_t kChunk = static_cast<int64_t>(kTpb) * kVec;
-  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  const int64_t chunk = static_cast<int64_t>(waves) * (64 * kVec);
+  const int64_t nchunks = waves < kWavesHere ? 1 : (n + chunk - 1) / chunk;   // the same in all waves of the workgroup
   // chunk c starts at lo(c): from the top for s > 0, from the bottom for s < 0
-  auto lo_of = [&](int64_t c) { return s > 0 ? n - (c + 1) * kChunk : c * kChunk; };
+  auto lo_of = [&](int64_t c) { return s > 0 ? n - (c + 1) * chunk : c * chunk; };
   u32x4 cur[kVec], nxt[kVec];
-  load_chunk<kVec, kTpb, kNt>(base, from, lo_of(0), n, cur);
+  load_chunk<kVec, kNt>(base, from, lo_of(0), n, wave, cur);
   for (int64_t c = 0; c < nchunks; ++c) {
     const bool more = c + 1 < nchunks;
-    if (more) load_chunk<kVec, kTpb, kNt>(base, from, lo_of(c + 1), n, nxt);
+    if (more) load_chunk<kVec, kNt>(base, from, lo_of(c + 1), n, wave, nxt);
 #pragma unroll
     for (int j = 0; j < kVec; ++j) hold(cur[j]);
     exec_barrier();  // every thread's loads of chunk c have landed
-    store_chunk<kVec, kTpb, kNt>(base, to, lo_of(c), n, cur);
+    store_chunk<kVec, kNt>(base, to, lo_of(c), n, wave, cur);
     if (more) {
 #pragma unroll
       for (int j = 0; j < kVec; ++j) cur[j] = nxt[j];
     }
   }
-  if (s > 0) {
+  if (s > 0 && !idle) {
     // the vacated columns [pad_in, pad_out) become padding; every read of
     // them landed before the last barrier
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    for (int64_t u0 = 0; u0 < to - from; u0 += kTpb) {
-      const int64_t w0 = u0 + static_cast<int64_t>(wave_index()) * 64;
+    for (int64_t u0 = 0; u0 < to - from; u0 += waves * 64) {
+      const int64_t w0 = u0 + static_cast<int64_t>(wave) * 64;
       const int lane = static_cast<int>(threadIdx.x & 63);
       if (w0 + lane < to - from) st16_at<(kNt & 2) != 0>(base + (from + w0), static_cast<uint32_t>(lane), zero);
     }
@@ -929,18 +1083,29 @@ __device__ __forceinline__ void zero_vectors(u32x4* at, int64_t count) {
 }
 
 // Moves the vectors [0, n) at `at` by `shift` with one workgroup, chunk after
-// chunk in the direction of the shift.
-template <int kVec, int kTpb, int kNt>
+// chunk in the direction of the shift; with kAhead the next chunk's loads are
+// issued before this one's stores, as in realign_inplace_kernel.
+template <int kVec, int kTpb, int kNt, bool kAhead>
 __device__ void walk_span(u32x4* at, int64_t n, int64_t shift) {
   constexpr int64_t kChunk = static_cast<int64_t>(kTpb) * kVec;
-  u32x4 v[kVec];
-  for (int64_t it = 0; it < n; it += kChunk) {
-    const int64_t lo = shift > 0 ? n - it - kChunk : it;
-    load_chunk<kVec, kTpb, kNt>(at, 0, lo, n, v);
+  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  const int wave = wave_index();
+  auto lo_of = [&](int64_t c) { return shift > 0 ? n - (c + 1) * kChunk : c * kChunk; };
+  u32x4 cur[kVec], nxt[kAhead ? kVec : 1];
+  if constexpr (kAhead) load_chunk<kVec, kNt>(at, 0, lo_of(0), n, wave, cur);
+  for (int64_t c = 0; c < nchunks; ++c) {
+    const bool more = c + 1 < nchunks;
+    if constexpr (!kAhead) load_chunk<kVec, kNt>(at, 0, lo_of(c), n, wave, cur);
+    else if (more) load_chunk<kVec, kNt>(at, 0, lo_of(c + 1), n, wave, nxt);
 #pragma unroll
-    for (int j = 0; j < kVec; ++j) hold(v[j]);
-    exec_barrier();   // every thread's loads have landed, and no later chunk's source meets this one's place
-    store_chunk<kVec, kTpb, kNt>(at, shift, lo, n, v);
+    for (int j = 0; j < kVec; ++j) hold(cur[j]);
+    exec_barrier();   // every thread's loads of chunk c have landed, and no later chunk's source meets its place
+    store_chunk<kVec, kNt>(at, shift, lo_of(c), n, wave, cur);
+    if constexpr (kAhead)
+      if (more) {
+#pragma unroll
+        for (int j = 0; j < kVec; ++j) cur[j] = nxt[j];
+      }
   }
   if (shift > 0) zero_vectors<kTpb, kNt>(at, shift);
 }
@@ -985,8 +1150,8 @@ __device__ __forceinline__ uint32_t spread(uint32_t i, uint32_t slots) {
 // belong; the d that belong to the neighbour chunk lie in the place that the
 // shift vacated (its first d vectors for a shift to higher addresses, its
 // last d for one to lower), and realign_strips_kernel hands them over.  Where
-// a chunk is shorter than 2 d (a shift of many columns), one workgroup walks
-// the span instead.
+// a chunk is shorter than 2 d (a shift of many columns), one workgroup of the
+// second launch walks the span instead.
 template <int kVec, int kTpb, int kNt, bool kMany>
 __device__ __forceinline__ void move_chunk(const RealignArgs& a, uint32_t span, int c, const RowGeom& geo) {
   constexpr int kChunk = kTpb * kVec;
@@ -1005,10 +1170,7 @@ __device__ __forceinline__ void move_chunk(const RealignArgs& a, uint32_t span, 
       const Chunks ch(n, kChunk);
       if (c >= ch.count) return;
       const int64_t d = shift < 0 ? -shift : shift;
-      if (ch.shortest() < 2 * d) {
-        if (c == 0) walk_span<4, kTpb, kNt>(at, n, shift);
-        return;
-      }
+      if (ch.shortest() < 2 * d) return;   // left to the launch that follows
       lo = ch.lo(c);
       len = static_cast<int>(ch.lo(c + 1) - lo);
       first = c == 0;
@@ -1083,7 +1245,14 @@ __global__ __launch_bounds__(kTpb) void realign_chunk_kernel(RealignArgs a) {
 // with the vectors that moved away from there.  A batch of strips is loaded
 // before any is stored; a strip's place holds the strip that was loaded
 // before it.
-template <int kTpb, int kNt>
+//
+// A span whose shift is too long for that is walked here.  kWalk is the walk of
+// few spans, 128 KB a turn with the next turn's loads ahead, which takes a CU's
+// registers for one workgroup; without it, for the many spans whose strips
+// want several workgroups on a CU, 64 KB a turn.  (128 spans of 1 MB moved 200
+// columns left, us a step: 98 with 16 KB a turn on the chunks' own launch, 62
+// so, 54 with realign_inplace_kernel.)
+template <int kTpb, int kNt, bool kWalk>
 __global__ __launch_bounds__(kTpb) void realign_strips_kernel(RealignArgs a, int most) {
   constexpr int kVec = 4;
   const uint32_t span = a.span_base + blockIdx.x;
@@ -1094,11 +1263,14 @@ __global__ __launch_bounds__(kTpb) void realign_strips_kernel(RealignArgs a, int
   const int64_t shift = static_cast<int64_t>(geo.pad_out - geo.pad_in) * vpc;
   const int64_t n = static_cast<int64_t>(geo.len) * vpc;
   if (shift == 0 || n <= most) return;
+  u32x4* at = a.dst + static_cast<int64_t>(span) * a.dst_span_vecs + static_cast<int64_t>(geo.pad_in) * vpc;
   const Chunks ch(n, most);
   const int64_t d64 = shift < 0 ? -shift : shift;
-  if (ch.shortest() < 2 * d64) return;   // walked
+  if (ch.shortest() < 2 * d64) {
+    walk_span<kWalk ? 32 : 16, kTpb, kNt, kWalk>(at, n, shift);
+    return;
+  }
   const uint32_t d = static_cast<uint32_t>(d64);
-  u32x4* at = a.dst + static_cast<int64_t>(span) * a.dst_span_vecs + static_cast<int64_t>(geo.pad_in) * vpc;
   // strips to hand over: count - 1, and to lower addresses the row's end
   const int64_t strips = ch.count - 1 + (shift < 0 ? 1 : 0);
   const int64_t total = strips * d64;
@@ -1313,7 +1485,9 @@ static VerifyArgs verify_args(const VerifyLaunch& p) {
   a.chunks = static_cast<int32_t>((p.V + a.chunk_elems - 1) / a.chunk_elems);
   a.order = p.write_order ? reinterpret_cast<int32_t*>(static_cast<char*>(p.workspace) + order_offset(p.B, p.k, p.V))
                           : nullptr;
-  a.order_classes = p.order_classes;
+  a.order_group = reinterpret_cast<int32_t*>(static_cast<char*>(p.workspace) + kOrderGroupOffset);
+  a.order_by_row = p.order_by_row;
+  a.order_even_len = p.order_even_len;
   return a;
 }
 
@@ -1387,27 +1561,38 @@ static void fill_token_args(RealignArgs& a, const RealignLaunch& p, int tpb) {
 }
 
 // The in-place plan, by the longest span a row can have and the number of
-// spans (the host does not know the rows' lengths).  Whole steps in us, one box
-// a line; walk 32 / 1: the walk with the order table, 32 rows at a time in 2
-// length classes / a row at a time in 7, so that the long rows of all layers
-// come first; chunks: of 64 KB up to 1536 spans, else of 128 KB, at most two
+// spans (the host does not know the rows' lengths).  us, one box a line; walk 32
+// / walk 1: the walk with the order table, 32 rows at a time in 2 length
+// classes / a row at a time in 7, so that the long rows of all layers come
+// first; chunks: of 64 KB up to 1536 spans, else of 128 KB, at most two
 // workgroups a CU (through LDS they do not use: more in flight spreads the
 // DRAM traffic and costs up to 15%) unless noted.
-//   spans of one chunk: to 22 KB, walk 32 237, chunks 77 (no limit to two); to
-//     60 KB, ragged 580 / 138 (no limit), even 288 / 243; 5..124 KB, ragged 511 /
-//     272, even ones of 77..124 KB 416 / 433
-//   longer, walk 32 / walk 1 / chunks: 128 spans to 2 MB 72 / 73 / 52; 256 to 2 MB
-//     114 / 112 / 105; 512 to 2 MB 208 / 191 / 190; 1024 to 2 MB 348 / 298 / 317;
-//     2048 to 0.9 MB 194 / 131 / 168 and 294 / 177 / 184, of 128..230 KB 109 / 113 /
-//     116; 4096 to 1 MB, ragged 356 / 266 / 278, even 772 / 767 / 794; 8192 to 1
-//     MB, ragged 593 / 478 / 500, even 1354 / 1350 / 1405; 16384 to 0.9 MB 790 /
-//     819 / 855
-// 32 rows at a time, the last layers' long rows start last; one row at a time,
-// neighbouring workgroups move distant spans, which costs where there are
-// enough spans to hide the last round.  A single row stays where it is in a
-// decoding loop (its padding is 0), so one launch that finds nothing to do is
-// the better one (13.3 us a step, 16.3 with the strips).  Without a table (`ordered` false: a
-// realignment alone, a sampled step) chunks take the place of walk 1.
+//   steps, spans of one chunk: to 22 KB, walk 32 237, chunks 77 (no limit to two); to
+//     60 KB, ragged 580 / 138 (no limit), even 288 / 243; 5..124 KB, ragged 605 /
+//     358, even ones of 77..124 KB 451 / 466, 65536 of 100..128 KB 1987 / 2105: one
+//     workgroup a CU takes 441 and 1978, but 476 for the ragged ones
+//   steps, longer, walk 32 / walk 1 / chunks, ragged (log-uniform from 16 KB) and
+//     even ones to 1 MB: 256 spans 15.7 / 13.7 / 19.1 and 71 / 70 / 71; 512 50 / 40 / 61
+//     and 116 / 128 / 118; 1024 112 / 88 / 114 and 270 / 287 / 273; 2048 249 / 165 / 203
+//     and 521 / 538 / 535; 4096 436 / 285 / 333 and 1034 / 1044 / 1020; 8192 586 / 556 /
+//     640 and 2032 / 2065 / 2050
+//   128 spans, the longer of two rows staying: the other one of 1 MB 48 / 48 / 37, of 0.1
+//     MB (1 MB possible) 24 / 24 / 28, both possible to 0.3 MB 23 / 23 / 20 and 15 /
+//     14 / 17
+// One row at a time, neighbouring workgroups move distant spans; 32 at a time,
+// the last layers' long rows start last.  So the walk's table says which,
+// where the spans are at most 8192 (beyond, there are enough to hide the last
+// round: 16384 to 0.9 MB 790 / 819 / 855): 32 where at least five rows move and
+// their lengths are long and within a quarter of each other (shorter even
+// ones, 4480 of 320 KB: 288 / 253).  Chunks are for 128 spans at most, half the
+// CUs' number.  Without a table (`ordered` false: a realignment alone, a
+// sampled step) the walk orders up to 64 rows itself; realignments, cache's
+// order / chunks / so: 256 spans 7.7 / 12.9 / 7.1 and 64 / 65 / 63; 512 44 / 54 / 33 and
+// 109 / 111 / 121; 1024 106 / 124 / 80 and 266 / 268 / 279; 4096 572 / 282 / 285 and 1064
+// / 1080 / 1036; 8192 679 / 554 / 558 and 2103 / 2176 / 2063.  More rows than that
+// go by chunks.  A single row stays where it is in a decoding loop (its
+// padding is 0), so one launch that finds nothing to do is the better one
+// (13.3 us a step, 16.3 with the strips).
 InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_in, bool ordered) {
   InplacePlan plan;
   const int64_t longest = W_in * (D / 8);   // a row holds at most W_in columns
@@ -1418,10 +1603,12 @@ InplacePlan inplace_plan(int64_t L, int64_t B, int64_t H, int64_t D, int64_t W_i
     plan.chunks = 1;
     return plan;
   }
-  if (longest > 32 * 256 && (B == 1 || nspans > (ordered ? 512 : 8192))) {   // the walk
-    plan.table = ordered;
-    plan.classes = nspans > 8192 ? 2 : kMaxOrderClasses - 1;
-    plan.row_group = nspans > 8192 ? 32 : 1;
+  const bool few = nspans <= kCus / 2 && longest >= 32 * 1024;
+  if (longest > 32 * 256 && (B == 1 || nspans > 8192 || (!few && (ordered || B <= 64)))) {   // the walk
+    plan.table = ordered && B > 1;
+    plan.sorted = !plan.table && B > 1 && nspans <= 8192;
+    plan.even_len = static_cast<int>(32 * 1024 / (D / 8));
+    plan.by_row = nspans > 8192 ? 0 : nspans > 384 ? 1 : 2;
     return plan;
   }
   InplacePlan walk = plan;
@@ -1462,7 +1649,10 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
   const InplacePlan& plan = p.plan;
   if (p.in_place && plan.table != (p.order != nullptr)) return hipErrorInvalidValue;   // a table unread, or missing
   a.order = p.in_place ? p.order : nullptr;
-  a.row_group = static_cast<uint32_t>(plan.row_group);
+  a.order_group = p.order_group;
+  a.row_group = plan.by_row == 0 ? 32u : plan.by_row == 2 ? 1u : plan.table ? 0u : 32u;
+  a.len_half = kInTpb * kInVec / 2 / a.vpc;
+  a.len_quarter = kInTpb * kInVec / 4 / a.vpc;
   a.span_rows = static_cast<uint32_t>(static_cast<int64_t>(p.L) * 2 * p.H);
   const bool by_chunk = p.in_place && plan.chunks > 0;
   const int tpb = by_chunk ? plan.tpb : (p.in_place ? kInTpb : kOopTpb);
@@ -1520,8 +1710,12 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
         const int64_t most = max_launch_items() / kInTpb;
         const int64_t n = nspans - s0 < most ? nspans - s0 : most;
         a.span_base = static_cast<uint32_t>(s0);
-        hipLaunchKernelGGL((realign_strips_kernel<kInTpb, kInNt>), dim3(static_cast<uint32_t>(n)), dim3(kInTpb), 0,
-                           stream, a, plan.vec * plan.tpb);
+        const dim3 grid(static_cast<uint32_t>(n)), block(kInTpb);
+        const int most_vecs = plan.vec * plan.tpb;
+        if (nspans <= kCus)
+          hipLaunchKernelGGL((realign_strips_kernel<kInTpb, kInNt, true>), grid, block, 0, stream, a, most_vecs);
+        else
+          hipLaunchKernelGGL((realign_strips_kernel<kInTpb, kInNt, false>), grid, block, 0, stream, a, most_vecs);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         s0 += n;
@@ -1541,8 +1735,10 @@ hipError_t launch_realign(const RealignLaunch& p, hipStream_t stream) {
     const int64_t blocks = ns * chunks + (first ? extra : 0);
     if (blocks == 0) break;
     const dim3 grid(static_cast<uint32_t>(blocks));
-    if (p.in_place)
-      hipLaunchKernelGGL((realign_inplace_kernel<kInVec, kInTpb, kInNt>), grid, block, 0, stream, a);
+    if (p.in_place && plan.sorted)
+      hipLaunchKernelGGL((realign_inplace_kernel<kInVec, kInTpb, kInNt, true>), grid, block, 0, stream, a);
+    else if (p.in_place)
+      hipLaunchKernelGGL((realign_inplace_kernel<kInVec, kInTpb, kInNt, false>), grid, block, 0, stream, a);
     else if (split == 64)
       hipLaunchKernelGGL((realign_oop_kernel<kOopVec, kOopTpb, 64, kOopNt>), grid, block, 0, stream, a);
     else if (split == 512)

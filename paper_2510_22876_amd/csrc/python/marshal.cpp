@@ -436,4 +436,15 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", "Native argument marsha
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module); }
+// built_for: the torch whose headers were inlined above and the ABI of the
+// library's declarations, for specdec.py to compare with what it has loaded.
+PyMODINIT_FUNC PyInit__marshal(void) {
+  PyObject* m = PyModule_Create(&module);
+  PyObject* built_for = m ? Py_BuildValue("(si)", SPECDEC_TORCH_VERSION, SPECDEC_ABI_VERSION) : nullptr;
+  if (!built_for || PyModule_AddObject(m, "built_for", built_for) < 0) {
+    Py_XDECREF(built_for);
+    Py_XDECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -8,7 +8,8 @@ it has not been built; there is no fallback.
 The calls of a decoding loop are marshalled by the extension module
 ``_marshal`` (csrc/python/marshal.cpp), which makes the same checks natively
 and hands anything it does not take as it stands back to the Python code here;
-where the module is not built, the Python code does it all.
+where the module is not built, or for another torch or ABI, the Python code
+does it all.
 """
 from __future__ import annotations
 
@@ -123,11 +124,15 @@ LIB_PATH = str(_LIB_PATH)
 
 def _load_native():
     """The native marshalling, calling the functions of ``lib``; None when it
-    is not built for this interpreter and torch."""
+    is not built for this interpreter (its file name says which), this torch
+    (whose tensors it reads by its headers) or the library's ABI."""
     try:
         from paper_2510_22876_amd import _marshal
+        built_for = _marshal.built_for
         device, raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
     except (ImportError, AttributeError):
+        return None
+    if built_for != (str(torch.__version__), lib.specdec_abi_version()):
         return None
     _marshal.connect(device, raw_stream,
                      {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in EXPORTED})

@@ -849,7 +849,10 @@ __device__ __forceinline__ void exec_barrier() { asm volatile("s_barrier" ::: "m
 // one row and then the next row's, so that no long walk starts last; where half
 // of them reach half of the longest and the spans are many, slab by slab, as
 // neighbouring workgroups on neighbouring spans matter more then.  Rows within
-// a quarter of the longest keep the cache's order, row_group at a time.  Spans
+// a quarter of the longest keep the cache's order: of up to 2048 spans with the
+// rows that stay in their places (1024 spans of 16 rows 246 us, as in the
+// cache's order without a look at the rows; 259 with them left out), beyond
+// that without them, row_group at a time (4096 spans 1013 -> 997).  Spans
 // of uneven rows that fit half or a quarter of a chunk go two or four to a
 // workgroup (6144 spans of 5 to 232 KB 155 -> 137 us).  What a workgroup spends
 // here counts: it has the CU to itself, and with the longest, the shortest and
@@ -896,6 +899,15 @@ struct OrderedRows {
     const uint32_t S = a.span_rows;
     uint32_t n = static_cast<uint32_t>(count), r;
     share = 1u;
+    if (even && a.nspans <= 2048u) {
+      const uint32_t H = static_cast<uint32_t>(a.H);
+      const uint32_t slab_row = lin / H;
+      const uint32_t slab = slab_row / static_cast<uint32_t>(a.B);
+      row_u = slab_row - slab * static_cast<uint32_t>(a.B);
+      j = slab * H + (lin - slab_row * H);
+      geometry_at(static_cast<int>(row_u), g);
+      return __builtin_amdgcn_readlane(moves ? 1 : 0, static_cast<int>(row_u)) != 0;
+    }
     if (even) {
       if (lin >= n * S) return false;
       const uint32_t H = static_cast<uint32_t>(a.H), R = a.row_group < n ? a.row_group : n;
@@ -943,11 +955,14 @@ struct OrderedRows {
     }
     const int i = __builtin_ctzll(__ballot(moves && rank == static_cast<int>(r)));
     row_u = static_cast<uint32_t>(i);
+    geometry_at(i, g);
+    return true;
+  }
+  __device__ __forceinline__ void geometry_at(int i, RowGeom& g) const {
     g.pad_in = __builtin_amdgcn_readlane(row.pad_in, i);
     g.pad_out = __builtin_amdgcn_readlane(row.pad_out, i);
     g.len = __builtin_amdgcn_readlane(row.len, i);
     g.w = __builtin_amdgcn_readlane(row.w, i);
-    return true;
   }
 };
 
@@ -1588,8 +1603,9 @@ static void fill_token_args(RealignArgs& a, const RealignLaunch& p, int tpb) {
 // CUs' number.  Without a table (`ordered` false: a realignment alone, a
 // sampled step) the walk orders up to 64 rows itself; realignments, cache's
 // order / chunks / so: 256 spans 7.7 / 12.9 / 7.1 and 64 / 65 / 63; 512 44 / 54 / 33 and
-// 109 / 111 / 121; 1024 106 / 124 / 80 and 266 / 268 / 279; 4096 572 / 282 / 285 and 1064
-// / 1080 / 1036; 8192 679 / 554 / 558 and 2103 / 2176 / 2063.  More rows than that
+// 109 / 111 / 109; 1024 106 / 124 / 80 and 266 / 268 / 266 (even ones keep the
+// cache's order up to 2048); 4096 572 / 282 / 285 and 1064 / 1080 / 1036; 8192 679 / 554
+// / 558 and 2103 / 2176 / 2063.  More rows than that
 // go by chunks.  A single row stays where it is in a decoding loop (its
 // padding is 0), so one launch that finds nothing to do is the better one
 // (13.3 us a step, 16.3 with the strips).

@@ -60,6 +60,8 @@ CASES = {
     "sorted_shares": (_case(8300, np.r_[8294, 4091, 4090, 4085, 2043, 2042, _rows(27, 0, 2060, 4)], H=3), "table", 1, "sorted"),
     "sorted_together": (_case(8200, _rows(64, 3800, 8194, 5), H=17), "table", 1, "sorted"),
     "sorted_together_shares": (_case(8400, np.r_[8394, _rows(50, 4200, 8394, 6), _rows(13, 0, 4000, 7)], H=18), "table", 1, "sorted"),
+    # even rows alone: beyond 2048 spans without the rows that stay, the second group a few rows
+    "sorted_even_many": (_case(8300, _rows(36, 8000, 8290, 14, 8294), H=32), "table", 1, "sorted"),
     "sorted_d24": (_case(2900, _rows(40, 100, 2894, 8), H=3, D=24), "table", 1, "sorted"),
     "far_left_walks": (_case(12000, _rows(40, 3000, 9000, 9), H=3), "table", 1, "sorted"),
     # chunks of 4096 vectors: lengths at their edges, shifts of both signs, shifts too long to hand over

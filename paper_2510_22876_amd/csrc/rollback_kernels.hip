@@ -200,8 +200,12 @@ __device__ __forceinline__ int sequence_of(int32_t r, int lo, int B, Load cu_out
 // (32 sequences, lengths log-uniform in 64..4096) without work, and the
 // dispatch of empty workgroups bounded the kernel: 1510 us a call, against
 // 1045 with this tiling (6.95 GB; 8 sequences of U[128, 1024], 6.0 GB: 917 and
-// 905).  The search costs a few dependent loads: 64 sequences of 64-byte rows
-// (138 MB in all) take 26.6 us instead of 24.6.
+// 905).  The search costs a few dependent loads, and a piece in which a
+// sequence begins more of them, unless it is the next one, which is tried
+// first: 64 sequences of 64-byte rows (125 MB in all) take 24.3 us instead of 24.0
+// with each sequence tiled for itself (26.1 with a search for every lane
+// beyond the first sequence), 256 sequences of 10..100 256-byte rows (518 MB)
+// 82 instead of 90 (86).
 __global__ __launch_bounds__(kTpb) void varlen_compact_kernel(VarlenArgs a) {
   const uint32_t b = blockIdx.x;
   auto cu_scalar = [&](int i) { return load_invariant(a.cu_out + i); };
@@ -216,10 +220,14 @@ __global__ __launch_bounds__(kTpb) void varlen_compact_kernel(VarlenArgs a) {
     if (r0 >= rows) return;
     const int first = sequence_of(static_cast<int32_t>(r0), 0, a.B, cu_scalar);
     const int64_t start = cu_scalar(first), end = cu_scalar(first + 1);
+    const int64_t next_end = cu_scalar(first + 2 < a.B ? first + 2 : a.B);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int64_t r = r0 + q * kTpb + threadIdx.x;
-      if (r < rows) a.pos[r] = r - (r < end ? start : cu_lane(sequence_of(static_cast<int32_t>(r), first, a.B, cu_lane)));
+      if (r >= rows) break;
+      int64_t of = r < end ? start : end;   // the first row of r's sequence
+      if (r >= next_end) of = cu_lane(sequence_of(static_cast<int32_t>(r), first, a.B, cu_lane));
+      a.pos[r] = r - of;
     }
     return;
   }
@@ -247,7 +255,14 @@ __global__ __launch_bounds__(kTpb) void varlen_compact_kernel(VarlenArgs a) {
     }
     const int64_t last = end < total ? end : total;
     int64_t si = p0 + t;
-    if (si >= last && si < total) {   // a later sequence's rows begin inside the piece
+    int64_t next_end = 0, next_move = 0;
+    if (last < total && p0 + kTpb > last) {   // the next sequence's rows begin inside the piece
+      next_end = static_cast<int64_t>(cu_scalar(seq + 2)) * a.row_vecs;
+      next_move = (static_cast<int64_t>(load_invariant(a.cu_in + seq + 1)) - cu_scalar(seq + 1)) * a.row_vecs;
+    }
+    if (si >= last && si < next_end) {
+      si += next_move;
+    } else if (si >= last && si < total) {    // and those of later ones
       const int q = sequence_of(row_of(si), seq, a.B, cu_lane);
       si += (static_cast<int64_t>(a.cu_in[q]) - cu_lane(q)) * a.row_vecs;
     } else {                          // lanes outside the slab read a vector that is there, and store nothing

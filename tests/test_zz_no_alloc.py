@@ -1,11 +1,12 @@
 """specdec_step_noalloc (the fused step on the library's own scratch, for
 callers that cannot allocate) against specdec_step with a caller workspace,
 through the C ABI: every output bit for bit, on consecutive calls that share
-the library scratch, each later one smaller.  The first two cases have
-logit rows longer than 16 KB (verification in the scan and merge launches,
-partial maxima in the scratch); the others verify in one launch (one
-workgroup per row, completion counted in the scratch), including planted
-ties, f16 logits, k = 0 and a row whose pad_in is out of range.  Both calls of a pair see
+the library scratch, each later one smaller.  With at most 256 logit rows and a
+small cache these are small steps: the vocabulary scan, its partial maxima in
+the scratch, then one launch that merges them and realigns (the one-launch
+verification, whose counts a small step leaves alone, is tested with larger
+batches in test_zz_no_alloc_large.py).  Included are planted ties, f16 logits,
+k = 0 and a row whose pad_in is out of range.  Both calls of a pair see
 identical input bytes and identically pre-filled output buffers, and the
 verification outputs are also checked against the oracle."""
 import numpy as np
@@ -103,14 +104,13 @@ def test_noalloc_step_equals_step(variant):
         _against_oracle(w, W_in, pad_in, logits, draft, got)
 
 
-def test_noalloc_consecutive_one_launch_verifications():
-    """Ten one-launch verifications in a row of changing batch size, each
-    equal to specdec_step: the realignment clears the completion counts that
-    the next call's verification starts from."""
+def test_noalloc_consecutive_small_steps():
+    """Ten small steps in a row of changing batch size, each equal to
+    specdec_step: what an earlier one left in the scratch is not read."""
     from paper_2510_22876_amd import specdec as sd
     for t, B in enumerate([8, 3, 8, 1, 5, 2, 8, 7, 1, 4]):
         w = _workload("vicuna7b", dict(B=B, V=5000 + 97 * t, L=1, H=2, D=16, prompt=("uniform", 8, 60)))
-        say(f"consecutive one-launch call {t}: B={B} V={w.V}")
+        say(f"consecutive small step {t}: B={B} V={w.V}")
         inp = _inputs(w, seed=40 + t)
         ref = _one(sd, w, *inp, "oop", noalloc=False)
         got = _one(sd, w, *inp, "oop", noalloc=True)
@@ -120,7 +120,7 @@ def test_noalloc_consecutive_one_launch_verifications():
 
 def test_noalloc_bad_pad_in_flagged_like_step():
     """A row whose pad_in lies outside [0, L] is flagged and left out of the
-    width by the one-launch verification exactly as by specdec_step."""
+    width by a small step on the library's scratch exactly as by specdec_step."""
     from paper_2510_22876_amd import specdec as sd
     w = _workload("vicuna7b", dict(B=4, V=3001, L=1, H=2, D=16, prompt=("uniform", 8, 60)))
     say("bad pad_in: B=4 V=3001, row 1 out of range")
@@ -153,14 +153,12 @@ def test_noalloc_rejects_beyond_its_scratch():
     assert int(o.w_new.cpu()[0]) == -99        # nothing ran
 
 
-@pytest.mark.parametrize("V", [5000, 32000], ids=["one_launch_verify", "two_launch_verify"])
+@pytest.mark.parametrize("V", [5000, 32000], ids=["short_rows", "long_rows"])
 def test_noalloc_step_replayed_from_a_graph(V):
     """The caller this entry point is for: the step captured once in a HIP
     graph and replayed on new inputs (eager copies and synchronisations in
     between), each replay equal to an eager specdec_step with a caller
-    workspace, bit for bit.  Replays of the one-launch verification rely on
-    the realignment launch clearing the completion counts for the next
-    replay."""
+    workspace, bit for bit (small steps, with logit rows of 10 and of 64 KB)."""
     from paper_2510_22876_amd import specdec as sd
     sd.timing_enable(False)     # kernel timers record events: none inside the capture
     w = _workload("vicuna7b", dict(B=6, V=V, L=2, H=2, D=64, prompt=("uniform", 16, 120)))

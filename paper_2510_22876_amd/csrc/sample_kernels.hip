@@ -7,21 +7,23 @@
 //                   the row maximum and the sum of exp((x - max) / T) of each
 //                   chunk (online: a thread rescales its sum when its maximum
 //                   grows), stored per chunk.
-//   sample_finish   one workgroup per (sequence, chunk of V/64 logits, at
-//                   least 2048).  Each merges the sequence's chunk statistics
+//   sample_finish   one workgroup per sequence, and one per (sequence, chunk of
+//                   V/64 logits, at least 2048).  Each merges the sequence's chunk statistics
 //                   into the normalisers of p_r = softmax(target_r / T) and
 //                   q_r = softmax(draft_r / T), accepts draft r iff
 //                   u_r * q_r(x_r) < p_r(x_r) (one lane per draft, first
-//                   rejection by ballot) and sums its chunk's weights of the
+//                   rejection by ballot).  The sequence's own workgroup stores
+//                   the accepted count, and the last of these to finish writes
+//                   the new width and paddings (Eq. (1), Eq. (2)), possibly
+//                   before any token is drawn.  A chunk's sums its weights of the
 //                   distribution to sample, the residual max(0, p_j - q_j)
 //                   after a rejection at j (and p_j, its fallback), p_k after
 //                   k acceptances, as the total of every tile of 2048 logits.
-//                   The last workgroup of a sequence to finish draws the token
+//                   The last chunk of a sequence to finish draws the token
 //                   by inversion with u_sample, coarse to fine: the chunk
 //                   totals (a prefix over at most 64 chunks in wave 0), the
 //                   tile totals of the crossing chunk, then one block-wide
-//                   scan of the crossing tile.  The last sequence to finish
-//                   writes the new width and paddings (Eq. (1), Eq. (2)).
+//                   scan of the crossing tile.
 //
 // Arithmetic is fp32 with exp2 of (x - max) * log2(e) / T; everything is
 // bandwidth- or latency-bound, no matrix cores.
@@ -119,8 +121,8 @@ struct SampleArgs {
   int32_t* pad_out;
   int32_t* w_new;
   float2* partial;           // [B*(2k+1)][chunks]: (max, sum of exp2((x - max) * c))
-  uint32_t* batch_count;     // sequences that have drawn their token
-  uint32_t* seq_count;       // [B * kCountStride]: finished workgroups of each sequence
+  uint32_t* batch_count;     // sequences whose accepted count is stored
+  uint32_t* seq_count;       // [B * kCountStride]: finished chunks of each sequence
   uint64_t* mass;            // [B][mchunks][tiles]: (residual weight, target weight) of each tile, as two floats
   uint64_t* last;            // [B][mchunks]: last index of positive residual / target weight, as two int32
   int64_t mchunk_elems;      // logits per mass chunk (a multiple of kGroup, or V)
@@ -138,7 +140,9 @@ constexpr int kCountStride = 4;   // words from one sequence's count to the next
 // all XCDs see.  A workgroup waits for its own stores and then counts itself
 // done; whoever counts last sees them all.  The count is relaxed: a
 // releasing one would write back the XCD's whole L2 (19 ns for each workgroup,
-// one after the other).
+// one after the other).  So every word that crosses workgroups here has to go
+// through put and get: a plain store may still lie in the writer's L2, a plain
+// load may hit an old line of the reader's.
 template <typename T>
 __device__ __forceinline__ void put(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -501,7 +505,7 @@ __device__ __forceinline__ int first_crossing(float v, int n, float base, float 
 }
 
 // New width and paddings (Eq. (1), Eq. (2)) from the accepted counts, by the
-// last workgroup of the launch.
+// last of the workgroups that store them.
 __device__ void width_and_pads(const SampleArgs& a, int32_t* red) {
   const int32_t L = a.W_in - (a.k + 1);
   int32_t local = 0;
@@ -532,12 +536,13 @@ __device__ void width_and_pads(const SampleArgs& a, int32_t* red) {
   if (threadIdx.x == 0) a.w_new[0] = w;
 }
 
-// One workgroup per (sequence, chunk), see the top of the file.  A residual
+// B workgroups that count and one per (sequence, chunk), see the top of the file.  A residual
 // with no mass falls back to p_j; where rounding leaves no crossing, the last
 // index of positive weight seen is taken.
 //
 // The accept tests are repeated by every workgroup of a sequence (its chunk
-// statistics are a few hundred bytes), and the drawing is left to the last one
+// statistics are (2k + 1) * chunks * 8 bytes: 5.5 KB at k = 5 and 63 chunks, 66 KB
+// at most), and the drawing is left to the last one
 // to finish, because a launch costs more than either: accept, mass and pick
 // kernels took 4.9 + 11.1 + 8.1 us at B = 64, k = 4, V = 151936 (bf16) and 4.0 +
 // 3.6 + 7.1 at B = 2, k = 5, V = 32000; this one takes 21.6 and 10 to 12, and two
